@@ -240,6 +240,7 @@ __global__ __launch_bounds__(kValuThreads) void split_valu_kernel(SplitArgs a) {
 #include "split_mfma.h"
 #include "split_slice.h"
 #include "split_wide.h"
+#include "split_f32.h"
 namespace egmla {
 
 // ---------------------------------------------------------------------------
@@ -433,6 +434,9 @@ int absorb_spin_limit() {
   return 1 << 16;
 }
 
+// Waves of the single-launch decode (one work-group per sequence and block of 16 heads).
+constexpr int kOneWaves = 8;
+
 // Balanced head-split kernel: `ranges` token ranges x a.groups blocks of 64 heads.
 // Wide kernel: units in flight per score wave.
 #ifndef EGMLA_WIDE_DEPTH
@@ -460,8 +464,28 @@ hipError_t launch_mfma(const SplitArgs& a, int nblocks, hipStream_t stream, hipE
   return hipGetLastError();
 }
 
-hipError_t launch_split(const eg_mla_dims& d, const DecodePlan& p, const SplitArgs& a, hipStream_t stream,
-                        hipEvent_t ev0, hipEvent_t ev1) {
+// fp32 matrix-core kernel: the smallest latent bucket that holds d_c.
+template <bool BF16>
+hipError_t launch_f32(const SplitArgs& a, const OneArgs& one, bool single, int nblocks, hipStream_t stream) {
+  if (single) {
+    if (a.DC <= 64)
+      hipLaunchKernelGGL((split_f32_kernel<BF16, 64, kOneWaves, true>), dim3(nblocks), dim3(kOneWaves * 64), 0, stream, a, one);
+    else
+      hipLaunchKernelGGL((split_f32_kernel<BF16, 128, kOneWaves, true>), dim3(nblocks), dim3(kOneWaves * 64), 0, stream, a, one);
+  } else if (a.DC <= 64) {
+    hipLaunchKernelGGL((split_f32_kernel<BF16, 64, 4, false>), dim3(nblocks), dim3(256), 0, stream, a, one);
+  } else if (a.DC <= 128) {
+    hipLaunchKernelGGL((split_f32_kernel<BF16, 128, 4, false>), dim3(nblocks), dim3(256), 0, stream, a, one);
+  } else if (a.DC <= 256) {
+    hipLaunchKernelGGL((split_f32_kernel<BF16, 256, 4, false>), dim3(nblocks), dim3(256), 0, stream, a, one);
+  } else {
+    hipLaunchKernelGGL((split_f32_kernel<BF16, 320, 4, false>), dim3(nblocks), dim3(256), 0, stream, a, one);
+  }
+  return hipGetLastError();
+}
+
+hipError_t launch_split(const eg_mla_dims& d, const DecodePlan& p, const SplitArgs& a, const OneArgs& one,
+                        hipStream_t stream, hipEvent_t ev0, hipEvent_t ev1) {
   const int64_t nblocks64 = static_cast<int64_t>(a.B) * a.s_max * a.groups;
   if (nblocks64 > 0x7fffffff) return hipErrorInvalidValue;
   const int nblocks = static_cast<int>(nblocks64);
@@ -476,6 +500,13 @@ hipError_t launch_split(const eg_mla_dims& d, const DecodePlan& p, const SplitAr
     return hipErrorInvalidValue;
   }
   if (ev0 && hipEventRecord(ev0, stream) != hipSuccess) return hipErrorInvalidValue;
+  if (p.f32_mfma) {
+    const int nb = p.one_launch ? a.B * a.groups : nblocks;
+    hipError_t e = d.dtype == EG_MLA_BF16 ? launch_f32<true>(a, one, p.one_launch, nb, stream)
+                                          : launch_f32<false>(a, one, p.one_launch, nb, stream);
+    if (e == hipSuccess && ev1) e = hipEventRecord(ev1, stream);
+    return e;
+  }
   const int DQ = d.latent_dim + d.rope_dim;
   size_t lds = sizeof(float) * (static_cast<size_t>(a.hpg) * DQ + kTile * (DQ + 1) + a.hpg * kTile + a.hpg + 1) +
                kTile * (sizeof(int64_t) + sizeof(int)) + 16;
@@ -528,15 +559,15 @@ eg_mla_status run_decode(const eg_mla_dims& d, const DecodePlan& p, int32_t batc
   const WideSchedArgs sched{seq_lens, p.capacity, p.balanced ? wide_groups(p.head_groups) : 0, sched_hdr, wg_start,
                             seq_rows};
   // 1. absorption (or inside the split kernel)
-  if (!p.fused_absorb) {
+  if (!p.fused_absorb && !p.one_launch) {
     dim3 grid(d.num_heads, (d.latent_dim + kAbsorbCols - 1) / kAbsorbCols, (batch + kAbsorbRows - 1) / kAbsorbRows);
     const size_t lds = sizeof(float) * (kAbsorbRows * d.head_dim + 4 * kAbsorbRows * kAbsorbCols);
-    if (bf && d.head_dim == 128) {
+    if (bf && (d.head_dim == 128 || d.head_dim == 64)) {
       // A W_UK of a few MB is read once per block of sequences: group blocks so
       // it is read about once; a small one is cheap to re-read, and one block
       // per work-group spreads the work over more compute units.
       const size_t wuk_bytes = static_cast<size_t>(d.num_heads) * d.head_dim * d.latent_dim * 2;
-      const bool grouped = p.balanced || wuk_bytes >= (size_t{4} << 20);
+      const bool grouped = p.balanced || (d.head_dim == 128 && wuk_bytes >= (size_t{4} << 20));
       const int rows = kAbsRows * (grouped ? kAbsBlocks : 1);
       const int row_blocks = (batch + rows - 1) / rows;
       // a small grid takes narrower column slices: more work-groups, each
@@ -550,7 +581,14 @@ eg_mla_status run_decode(const eg_mla_dims& d, const DecodePlan& p, int32_t batc
         hipLaunchKernelGGL((absorb_mfma_kernel<128, kAbsBlocks, kAbsCols, true>), dim3(ga.x + 1, ga.y, ga.z),
                            dim3(256), 0, stream, q16, wuk16, qfull, batch, d.num_heads, d.latent_dim, d.rope_dim,
                            sched);
-      else if (grouped)
+      else if (d.head_dim == 64) {
+        if (narrow)
+          hipLaunchKernelGGL((absorb_mfma_kernel<64, 1, kAbsColsNarrow>), ga, dim3(256), 0, stream, q16, wuk16, qfull,
+                             batch, d.num_heads, d.latent_dim, d.rope_dim, sched);
+        else
+          hipLaunchKernelGGL((absorb_mfma_kernel<64, 1, kAbsCols>), ga, dim3(256), 0, stream, q16, wuk16, qfull,
+                             batch, d.num_heads, d.latent_dim, d.rope_dim, sched);
+      } else if (grouped)
         hipLaunchKernelGGL((absorb_mfma_kernel<128, kAbsBlocks, kAbsCols>), ga, dim3(256), 0, stream, q16, wuk16,
                            qfull, batch, d.num_heads, d.latent_dim, d.rope_dim, sched);
       else if (narrow)
@@ -612,7 +650,17 @@ eg_mla_status run_decode(const eg_mla_dims& d, const DecodePlan& p, int32_t batc
     }
     hipEvent_t ev0 = plan ? static_cast<hipEvent_t>(plan->split_start_event) : nullptr;
     hipEvent_t ev1 = plan ? static_cast<hipEvent_t>(plan->split_stop_event) : nullptr;
-    if (launch_split(d, p, a, stream, ev0, ev1) != hipSuccess) return EG_MLA_ERR_HIP;
+    OneArgs one{q, w_uk, w_uv, out, d.v_head_dim, 1, 1};
+    if (p.one_launch) {
+      // enough slices of the head dim, and threads per output, to occupy the work-group
+      const int nt = kOneWaves * 64, nh = std::min(d.num_heads, 16);
+      const int tasks = nh * (d.latent_dim / (16 / elem_bytes(d)));
+      one.slices = std::max(1, std::min(nt / tasks, d.head_dim));
+      while (one.tpo < 8 && 2 * one.tpo * nh * d.v_head_dim <= nt) one.tpo *= 2;
+      a.split = p.capacity;  // the whole context is one split
+    }
+    if (launch_split(d, p, a, one, stream, ev0, ev1) != hipSuccess) return EG_MLA_ERR_HIP;
+    if (p.one_launch) return EG_MLA_OK;
   }
   // 3. combine + W_UV
   {

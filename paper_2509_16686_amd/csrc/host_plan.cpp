@@ -12,6 +12,13 @@ constexpr int kTargetWorkItems = 1024;
 // Token-split MFMA kernel: one 4-wave work-group per compute unit streams
 // longest without gaps between its loads (256 compute units).
 constexpr int kTargetWorkItemsTok = 256;
+// fp32 matrix-core kernel: 4-wave work-groups, two per compute unit up to
+// d_c 64; above, a work-group's LDS leaves room for one (measured at batch 32,
+// d_c 256, lengths to 3003: 384-token splits 42.0 us per call, 192-token 48.7).
+constexpr int kTargetWorkItemsF32 = 512;
+
+// Single-launch form: W_UK (and W_UV) bytes of a block of heads, at most.
+constexpr int64_t kOneMaxWeightBytes = 128 * 1024;
 
 int ceil_div(int64_t a, int64_t b) { return static_cast<int>((a + b - 1) / b); }
 bool aligned16(const void* p) { return reinterpret_cast<uintptr_t>(p) % 16 == 0; }
@@ -29,6 +36,8 @@ bool heads_kernel_shape(const eg_mla_dims& d) {
   return d.latent_dim == 512 && d.rope_dim == 64 && d.head_dim == 128 && d.v_head_dim == 128 &&
          d.num_heads % kHeadsPerItemWide == 0;
 }
+
+bool f32_kernel_shape(const eg_mla_dims& d) { return d.latent_dim <= 320 && d.rope_dim <= 64; }
 
 eg_mla_status check_dims(const eg_mla_dims* d) {
   if (!d) return EG_MLA_ERR_INVALID_ARG;
@@ -61,8 +70,14 @@ eg_mla_status make_decode_plan(const eg_mla_dims& d, int32_t batch, int32_t max_
   if (cap64 > (1 << 30)) return EG_MLA_ERR_INVALID_ARG;
   p.capacity = static_cast<int>(cap64);
 
+  // The vector kernel stays for the shapes the fp32 matrix-core kernel does
+  // not take, for explicit splits past its token list, and when asked for.
+  p.f32_mfma = p.path == EG_MLA_PATH_VALU && forced == EG_MLA_PATH_AUTO && f32_kernel_shape(d) &&
+               (plan == nullptr || plan->split_tokens <= kMaxSplitTokens);
   if (p.path == EG_MLA_PATH_MFMA) {
     p.heads_per_group = heads_kernel_shape(d) ? kHeadsPerItemWide : 16;
+  } else if (p.f32_mfma) {
+    p.heads_per_group = 16;
   } else {
     // Heads per VALU work item: at most 8192 latent accumulators per workgroup.
     p.heads_per_group = std::max(1, std::min({d.num_heads, 8192 / d.latent_dim, 256}));
@@ -86,17 +101,27 @@ eg_mla_status make_decode_plan(const eg_mla_dims& d, int32_t batch, int32_t max_
     const int64_t work =
         static_cast<int64_t>(std::max(batch, 1)) * std::max(p.capacity, 1) * p.head_groups * p.slices;
     const int64_t target =
-        p.path == EG_MLA_PATH_MFMA && (tok_kernel_shape(d) || heads_kernel_shape(d)) ? kTargetWorkItemsTok : kTargetWorkItems;
+        p.path == EG_MLA_PATH_MFMA && (tok_kernel_shape(d) || heads_kernel_shape(d)) ? kTargetWorkItemsTok
+        : p.f32_mfma ? (d.latent_dim <= 64 ? kTargetWorkItemsF32 : kTargetWorkItemsF32 / 2)
+                     : kTargetWorkItems;
     int64_t s = (work + target - 1) / target;
     const int gran = p.slices > 1 ? 256 : kTile;  // sliced kernel: whole 256-position scan rows
     s = (s + gran - 1) / gran * gran;
-    const int min_split = p.path == EG_MLA_PATH_MFMA ? 256 : 128;
+    const int min_split = p.path == EG_MLA_PATH_MFMA || p.f32_mfma ? 256 : 128;
     s = std::max<int64_t>(s, min_split);
     s = std::min<int64_t>(s, max_split);
     split = static_cast<int>(s);
   }
   p.split_tokens = split;
   p.s_max = std::max(1, ceil_div(std::max(p.capacity, 1), split));
+  // One launch instead of three where a work-group can afford its heads'
+  // weights (read whole by every sequence) and its whole context, and all
+  // work-groups are resident at once.
+  p.one_launch = p.f32_mfma && (plan == nullptr || plan->split_tokens == 0) && p.capacity > 0 &&
+                 p.capacity <= kOneMaxTokens && d.latent_dim <= kOneMaxLatent &&
+                 static_cast<int64_t>(std::min(d.num_heads, 16)) * std::max(d.head_dim, d.v_head_dim) * d.latent_dim *
+                         elem_bytes(d) <= kOneMaxWeightBytes &&
+                 static_cast<int64_t>(std::max(batch, 0)) * p.head_groups <= kTargetWorkItemsF32;
   // The head-split kernel balances tokens over its work-groups whatever the
   // length mix; its split size only caps the token list it stages at a time.
   p.balanced = p.path == EG_MLA_PATH_MFMA && heads_kernel_shape(d);

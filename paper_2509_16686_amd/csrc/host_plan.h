@@ -32,6 +32,11 @@ bool tok_kernel_shape(const eg_mla_dims& d);
 // dimension-split kernel (16 heads per work item).
 bool heads_kernel_shape(const eg_mla_dims& d);
 constexpr int kHeadsPerItemWide = 64;
+// Shapes of the fp32 matrix-core kernel (any head count and storage type), and
+// the largest context and latent dim of its single-launch form.
+bool f32_kernel_shape(const eg_mla_dims& d);
+constexpr int kOneMaxTokens = 512;
+constexpr int kOneMaxLatent = 128;
 // Balanced schedule of the head-split kernel: at most this many token ranges
 // (one work-group per range and block of 64 heads, one per compute unit of the
 // device over all head blocks).
@@ -46,6 +51,8 @@ struct DecodePlan {
   int heads_per_group = 0;
   int slices = 1;               // partials per (b, split, head group): token-id slices of the sliced kernel
   bool balanced = false;        // head-split kernel: balanced schedule (split_tokens = list chunk)
+  bool f32_mfma = false;        // VALU-path shape served by the fp32 matrix-core kernel (split_f32.h)
+  bool one_launch = false;      // ... in its single-launch form (absorption and up-projection inside)
   bool fused_absorb = false;    // d_c 128 split kernel absorbs the query itself (no id slices, d_h 128)
   // workspace layout (byte offsets)
   size_t off_q = 0;     // fp32 [B, H, d_c + d_r]  absorbed query | RoPE query
