@@ -34,6 +34,9 @@
 
 namespace egmla {
 
+// Stamps and bitmap words one 128-byte line apart, so that atomics of
+// different ones do not queue on one line.
+constexpr int kMarkStride = 32;
 constexpr int kGateThreads = 256;        // VALU kernel
 constexpr int kGateWaves = 8;            // MFMA kernel: waves per work-group (2 per SIMD)
 constexpr int kGateLdsBudget = 150 * 1024;  // bytes of W^UE slice in LDS, at most
@@ -83,10 +86,10 @@ __device__ __forceinline__ void gate_store(const gate_f32x16_t (&acc)[NCB], uint
     }
 }
 
-// TABLE: `ids` is the list of distinct ids that gate_claim_kernel built, its
-// length counts[parity] (read on the device; n bounds it), and row i writes
-// out[ids[i]], a [V, d_c] table.  Thread 0 zeroes counts[parity ^ 1], the
-// slot of the next call.
+// TABLE: `ids` is the list of distinct ids that pass 1 built, its length
+// counts[parity] (read on the device; n bounds it), and row i writes
+// out[ids[i]], a [V, d_c] table.  The kernel zeroes what the next call's pass 1
+// starts from: counts[parity ^ 1] and the nclear words of `clear`, a line apart.
 template <int EP, int NCB, bool ONE_PASS, bool TABLE = false>
 __global__ __launch_bounds__(64 * kGateWaves, 1) void gate_rows_mfma_kernel(const int32_t* __restrict__ ids,
                                                                             const uint16_t* __restrict__ emb,
@@ -94,9 +97,13 @@ __global__ __launch_bounds__(64 * kGateWaves, 1) void gate_rows_mfma_kernel(cons
                                                                             uint16_t* __restrict__ out, int64_t n,
                                                                             int E, int DC, int V, int S,
                                                                             unsigned int* __restrict__ counts,
-                                                                            unsigned int parity) {
+                                                                            unsigned int parity,
+                                                                            unsigned int* __restrict__ clear,
+                                                                            int nclear) {
   if constexpr (TABLE) {
     n = min(n, static_cast<int64_t>(counts[parity]));
+    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < nclear; i += gridDim.x * blockDim.x)
+      clear[static_cast<int64_t>(i) * kMarkStride] = 0u;
     if (blockIdx.x == 0 && threadIdx.x == 0) counts[parity ^ 1u] = 0u;
   }
   if (n <= 0) return;  // uniform over the work-group
@@ -179,9 +186,6 @@ __global__ __launch_bounds__(64 * kGateWaves, 1) void gate_rows_mfma_kernel(cons
   }
 }
 
-// Stamp slots one 128-byte line apart, so that claims of different ids do
-// not queue on one line.
-constexpr int kMarkStride = 32;
 constexpr int kClaimThreads = 1024;
 
 // Distinct ids of a list (pass 1 of eg_mla_gate_table): row i claims its id
@@ -217,6 +221,84 @@ __global__ __launch_bounds__(kClaimThreads) void gate_claim_kernel(const int32_t
   for (int k = 0; k < w; ++k) before += wave_n[k];
   const unsigned int pos = before + static_cast<unsigned int>(__builtin_popcountll(mask & ((uint64_t{1} << lane) - 1)));
   if (win && pos < static_cast<unsigned int>(V)) list[pos] = id;  // a counter left nonzero cannot overrun
+}
+
+// Distinct ids by bitmap (pass 1 of eg_mla_gate_table for vocabularies whose
+// bitmap fits the LDS).  Each work-group marks the ids of its rows in an LDS
+// bitmap, ORs each nonzero word into the call's global one (one returning
+// atomic per word) and appends the bits that were not set there to the list,
+// its places reserved with one atomic add.  The id line above costs one global
+// atomic per row, most of them repeats: 539 K rows of 50304 ids took 26.6 us;
+// here it is at most one per work-group and word, in 9.2 us.
+// bits: this call's words (a line apart), zero on entry; the list pass
+// zeroes the other call parity's.
+constexpr int kBitmapMaxWords = 16384;  // 64 KB of LDS: vocabularies up to 524288
+constexpr int kBitmapRows = 2048;       // rows of a work-group, at least
+constexpr int kBitmapGroups = 40;       // work-groups, at most: more repeat each other's words (64: 10.0 us, 128: 13.2)
+
+__global__ __launch_bounds__(kClaimThreads) void gate_bitmap_kernel(const int32_t* __restrict__ ids, int64_t n, int V,
+                                                                    int nwords, unsigned int* __restrict__ bits,
+                                                                    unsigned int* __restrict__ count,
+                                                                    int32_t* __restrict__ list) {
+  extern __shared__ __attribute__((aligned(16))) unsigned int word[];  // [nwords]
+  __shared__ unsigned int wave_n[kClaimThreads / 64];
+  __shared__ unsigned int wg_base;
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  for (int j = tid; j < nwords; j += kClaimThreads) word[j] = 0u;
+  const int64_t per = (n + gridDim.x - 1) / gridDim.x;
+  const int64_t i0 = per * blockIdx.x, i1 = min(n, i0 + per);
+  __syncthreads();
+  for (int64_t base = i0; base < i1; base += 8 * kClaimThreads) {
+    int id[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) id[u] = ids[min(base + u * kClaimThreads + tid, i1 - 1)];  // past the end: the last again
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      if (base + u * kClaimThreads + tid >= i1) continue;
+      const int v = clamp_id(id[u], V);
+      atomicOr(word + (v >> 5), 1u << (v & 31));
+    }
+  }
+  __syncthreads();
+  // this thread's words, starting elsewhere in each work-group; a word is kept as its newly set bits
+  const int rot = static_cast<int>(static_cast<int64_t>(nwords) * blockIdx.x / gridDim.x);
+  unsigned int mine = 0;
+#pragma unroll 4
+  for (int k = tid; k < nwords; k += kClaimThreads) {
+    const int j = k + rot < nwords ? k + rot : k + rot - nwords;
+    unsigned int x = word[j];
+    if (x != 0u) {
+      x &= ~atomicOr(bits + static_cast<int64_t>(j) * kMarkStride, x);
+      word[j] = x;
+    }
+    mine += static_cast<unsigned int>(__builtin_popcount(x));
+  }
+  unsigned int pre = mine;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const unsigned int y = __shfl_up(pre, o, 64);
+    if (lane >= o) pre += y;
+  }
+  if (lane == 63) wave_n[w] = pre;
+  __syncthreads();
+  if (tid == 0) {
+    unsigned int tot = 0;
+    for (int k = 0; k < kClaimThreads / 64; ++k) tot += wave_n[k];
+    wg_base = tot > 0 ? atomicAdd(count, tot) : 0u;
+  }
+  __syncthreads();
+  unsigned int pos = wg_base + pre - mine;
+  for (int k = 0; k < w; ++k) pos += wave_n[k];
+  for (int k = tid; k < nwords; k += kClaimThreads) {
+    const int j = k + rot < nwords ? k + rot : k + rot - nwords;
+    unsigned int x = word[j];  // written by this thread
+    while (x != 0u) {
+      const int id = 32 * j + __builtin_ctz(x);
+      x &= x - 1u;
+      if (pos < static_cast<unsigned int>(V)) list[pos] = id;  // a counter left nonzero cannot overrun
+      ++pos;
+    }
+  }
 }
 
 // TABLE: row i writes out[ids[i]] (rows with the same id write the same bits)
@@ -282,13 +364,28 @@ eg_mla_status launch_gate(const eg_mla_dims* dims, int32_t emb_dim, int32_t emb_
   const bool mfma = gs.S > 0 && reinterpret_cast<uintptr_t>(emb) % 16 == 0 &&
                     reinterpret_cast<uintptr_t>(w_ue) % 16 == 0 && reinterpret_cast<uintptr_t>(out) % 8 == 0;
   unsigned int* counts = nullptr;
+  unsigned int* clear = nullptr;
+  int nclear = 0;
   if (mfma && table) {
-    // pass 1: the distinct ids into a list (marks: [V] stamp lines, [2] counts, [V] list)
+    // pass 1: the distinct ids into a list (marks: [V] lines of stamps or bitmap words, [2] counts, [V] list)
     if (n > (int64_t{1} << 40)) return EG_MLA_ERR_UNSUPPORTED;
     unsigned int* cnt = marks + static_cast<int64_t>(emb_vocab) * kMarkStride;
     int32_t* list = reinterpret_cast<int32_t*>(cnt + 2);
-    hipLaunchKernelGGL(gate_claim_kernel, dim3(static_cast<unsigned>((n + kClaimThreads - 1) / kClaimThreads)),
-                       dim3(kClaimThreads), 0, stream, ids, n, emb_vocab, marks, stamp, list);
+    const int nwords = (emb_vocab + 31) / 32;
+    // (the same pass for every call of a vocabulary: the two keep different
+    // things in the marks, whose V stamp lines hold the 2 ceil(V / 32) bitmap words from V = 2 on)
+    if (emb_vocab >= 2 && nwords <= kBitmapMaxWords) {
+      unsigned int* bits[2] = {marks, marks + static_cast<int64_t>(nwords) * kMarkStride};
+      const int64_t groups = std::max<int64_t>(1, std::min<int64_t>(kBitmapGroups, n / kBitmapRows));
+      hipLaunchKernelGGL(gate_bitmap_kernel, dim3(static_cast<unsigned>(groups)), dim3(kClaimThreads),
+                         nwords * sizeof(unsigned int), stream, ids, n, emb_vocab, nwords, bits[stamp & 1u],
+                         cnt + (stamp & 1u), list);
+      clear = bits[(stamp & 1u) ^ 1u];
+      nclear = nwords;
+    } else {
+      hipLaunchKernelGGL(gate_claim_kernel, dim3(static_cast<unsigned>((n + kClaimThreads - 1) / kClaimThreads)),
+                         dim3(kClaimThreads), 0, stream, ids, n, emb_vocab, marks, stamp, list);
+    }
     counts = cnt;
     ids = list;
     n = std::min<int64_t>(n, emb_vocab);  // the list holds distinct ids only
@@ -329,7 +426,7 @@ eg_mla_status launch_gate(const eg_mla_dims* dims, int32_t emb_dim, int32_t emb_
     int V = emb_vocab, Ev = E, DCv = DC, Sv = S;
     unsigned int* counts_c = counts;
     unsigned int parity = stamp & 1u;
-    void* args[] = {&ids_c, &emb_c, &w_c, &out_c, &n, &Ev, &DCv, &V, &Sv, &counts_c, &parity};
+    void* args[] = {&ids_c, &emb_c, &w_c, &out_c, &n, &Ev, &DCv, &V, &Sv, &counts_c, &parity, &clear, &nclear};
     if (hipLaunchKernel(fn, dim3(grid), dim3(64 * kGateWaves), args, lds, stream) != hipSuccess)
       return EG_MLA_ERR_HIP;
   } else {
