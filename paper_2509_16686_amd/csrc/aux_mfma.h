@@ -20,6 +20,10 @@ namespace egmla {
 // issued before the first use.  bf16 x bf16 products are exact in fp32 and
 // accumulate in fp32.
 // ---------------------------------------------------------------------------
+struct SchedArgs {
+  WideSchedArgs wide;
+  TokSchedArgs tok;
+};
 constexpr int kAbsRows = 16;    // sequences per MFMA row block
 constexpr int kAbsBlocks = 4;   // row blocks per work-group, at most
 constexpr int kAbsCols = 128;     // latent columns per work-group, at most
@@ -29,19 +33,22 @@ constexpr int kAbsMinWorkGroups = 128;
 
 // HALF: instead of fp32 rows [B, H, DC + DR], write 16-bit rows [B, H, DC + DR]
 // = [q_lat in fp16 (one rounding) | q^R in bf16 (copied)], the operands of the
-// wide kernel's fp16 latent product and exact bf16 RoPE product; the grid then
-// has one more column of work-groups (blockIdx.x == H), the first of which
-// computes the wide kernel's balanced schedule from the lengths (sa).
-template <int DH, int BLOCKS, int COLS, bool HALF = false>
+// wide kernel's fp16 latent product and exact bf16 RoPE product.
+// SCHED: the grid has one more column of work-groups (blockIdx.x == H), the
+// first of which computes the balanced schedule from the lengths (sa).
+// (HALF: the wide kernel's schedule, otherwise the d_c 128 kernel's)
+template <int DH, int BLOCKS, int COLS, bool HALF = false, bool SCHED = HALF>
 __global__ __launch_bounds__(256) void absorb_mfma_kernel(const uint16_t* __restrict__ q,
                                                           const uint16_t* __restrict__ w_uk,
                                                           float* __restrict__ qfull, int B, int H, int DC, int DR,
-                                                          WideSchedArgs sa) {
+                                                          SchedArgs sa) {
   static_assert(BLOCKS >= 1 && BLOCKS <= kAbsBlocks, "row blocks per work-group");
-  if constexpr (HALF) {
-    // the extra column of work-groups: the head-split kernel's schedule
+  if constexpr (SCHED) {
     if (blockIdx.x == H) {
-      if (blockIdx.y == 0 && blockIdx.z == 0) wide_schedule<256>(sa, B);
+      if (blockIdx.y == 0 && blockIdx.z == 0) {
+        if constexpr (HALF) wide_schedule<256>(sa.wide, B);
+        else tok_schedule<256>(sa.tok, B);
+      }
       return;
     }
   }
@@ -543,8 +550,9 @@ template <int DC, int DV, typename Wait>
 __device__ __forceinline__ void combine4_block(const float* __restrict__ part_ml, const float* __restrict__ part_o,
                                                const uint16_t* __restrict__ w_uv,
                                                const int32_t* __restrict__ seq_lens, uint16_t* __restrict__ out,
-                                               int B, int H, int cap, int split, int s_max, int slices, int h,
-                                               int b0, uint16_t* o_s, Wait wait) {
+                                               int B, int H, int cap, int split, int s_max, int slices,
+                                               const int2* __restrict__ seq_rows, int h, int b0, uint16_t* o_s,
+                                               Wait wait) {
   constexpr int OS = DC + 8;  // bf16 elements: o / l hi in rows 0 .. 3, lo in rows 4 .. 7
   constexpr int PER = DC / 64;
   constexpr int NKC = DC / 32;
@@ -567,15 +575,25 @@ __device__ __forceinline__ void combine4_block(const float* __restrict__ part_ml
   // (2) wave w merges sequence b0 + w
   {
     const int b = b0 + w;
-    const int L = w < nseq ? clamp_len(seq_lens[b], cap) : 0;
-    const int ns = L > 0 ? min((L + split - 1) / split, s_max) * slices : 0;
+    int ns = 0;
+    int64_t row0 = static_cast<int64_t>(b) * s_max * slices;
+    if (w < nseq) {
+      if (seq_rows) {
+        const int2 sr = seq_rows[b];
+        row0 = sr.x;
+        ns = sr.y;
+      } else {
+        const int L = clamp_len(seq_lens[b], cap);
+        ns = L > 0 ? min((L + split - 1) / split, s_max) * slices : 0;
+      }
+    }
     float M = -INFINITY, Ls = 0.f;
     float acc[PER];
 #pragma unroll
     for (int j = 0; j < PER; ++j) acc[j] = 0.f;
     if (w < nseq) wait(b);
     if (ns > 0) {
-      const int64_t base = static_cast<int64_t>(b) * s_max * slices * H + h;
+      const int64_t base = row0 * H + h;
       if (ns <= 8) {
         merge_batch<DC, 8>(part_ml, part_o, base, H, 0, 1, 0, ns, lane, M, Ls, acc);
       } else {
@@ -625,9 +643,9 @@ template <int DC, int DV>
 __global__ __launch_bounds__(256) void combine4_kernel(const float* __restrict__ part_ml, const float* __restrict__ part_o,
                                                        const uint16_t* __restrict__ w_uv, const int32_t* __restrict__ seq_lens,
                                                        uint16_t* __restrict__ out, int B, int H, int cap, int split,
-                                                       int s_max, int slices) {
+                                                       int s_max, int slices, const int2* __restrict__ seq_rows) {
   __shared__ __attribute__((aligned(16))) uint16_t o_s[2 * kComb4Seq * (DC + 8)];
-  combine4_block<DC, DV>(part_ml, part_o, w_uv, seq_lens, out, B, H, cap, split, s_max, slices, blockIdx.x,
+  combine4_block<DC, DV>(part_ml, part_o, w_uv, seq_lens, out, B, H, cap, split, s_max, slices, seq_rows, blockIdx.x,
                          blockIdx.y * kComb4Seq, o_s, [](int) {});
 }
 

@@ -107,6 +107,7 @@ struct SplitArgs {
   float* part_o;              // [rows, H, DC]
   const int64_t* sched_hdr;   // balanced schedule (wide kernel): total tokens, work-groups
   const int2* wg_start;       // balanced schedule: (sequence, offset) where each work-group starts
+  const int4* tok_pieces;     // balanced schedule of the d_c 128 kernel
   int64_t num_slots;
   int B, H, DC, DR, P, max_pages, V, cap, split, s_max, groups, hpg;
   float scale_log2;           // softmax scale * log2(e)
@@ -339,11 +340,13 @@ hipError_t launch_combine_dc(dim3 grid, hipStream_t stream, const float* pm, con
   // Small work-groups when every sequence's partials fit one merge batch and
   // the grid stays within two work-groups per compute unit (measured faster
   // there; many partials per sequence, or many work-groups, favour the
-  // 16-wave kernel).
+  // 16-wave kernel).  The balanced schedule of the d_c 128 kernel leaves a
+  // sequence of average length at most 512 / B pieces: the small ones too
+  // (64 sequences of 2048: 4.0 against 5.5 us).
   const int64_t small_wg = static_cast<int64_t>(H) * ((B + kComb4Seq - 1) / kComb4Seq);
-  if (!seq_rows && static_cast<int64_t>(s_max) * slices <= 8 && small_wg <= 512) {
+  if ((seq_rows ? DC == 128 : static_cast<int64_t>(s_max) * slices <= 8) && small_wg <= 512) {
     hipLaunchKernelGGL((combine4_kernel<DC, 128>), dim3(H, (B + kComb4Seq - 1) / kComb4Seq), dim3(256), 0, stream,
-                       pm, po, wv, seq_lens, ov, B, H, cap, split, s_max, slices);
+                       pm, po, wv, seq_lens, ov, B, H, cap, split, s_max, slices, seq_rows);
     return hipGetLastError();
   }
   const size_t lds = combine_lds_bytes(DC);
@@ -398,9 +401,12 @@ namespace {
 // The MFMA split kernels launch with hipExtLaunchKernelGGL so that optional
 // timing events are stamped by the dispatch itself (kernel start and end).
 template <int DC, int DR>
-hipError_t launch_slice(const SplitArgs& a, int slices, int nblocks, hipStream_t stream, hipEvent_t ev0,
+hipError_t launch_slice(const SplitArgs& a, int slices, int pieces, int nblocks, hipStream_t stream, hipEvent_t ev0,
                         hipEvent_t ev1) {
-  if (slices == kIdSlices)
+  if (pieces > 0)
+    hipExtLaunchKernelGGL((split_slice_kernel<DC, DR, kSliceWaves, kSliceDepth, 1, false, true>),
+                          dim3(pieces * a.groups), dim3(kSliceWaves * 64), 0, stream, ev0, ev1, 0, a);
+  else if (slices == kIdSlices)
     hipExtLaunchKernelGGL((split_slice_kernel<DC, DR, kSliceWaves, kSliceDepth, kIdSlices>), dim3(nblocks * slices),
                           dim3(kSliceWaves * 64), 0, stream, ev0, ev1, 0, a);
   else if (a.qin)
@@ -492,7 +498,7 @@ hipError_t launch_split(const eg_mla_dims& d, const DecodePlan& p, const SplitAr
   if (p.path == EG_MLA_PATH_MFMA) {
     if (tok_kernel_shape(d)) {
       if (static_cast<int64_t>(nblocks) * p.slices > 0x7fffffff) return hipErrorInvalidValue;
-      return launch_slice<128, 64>(a, p.slices, nblocks, stream, ev0, ev1);
+      return launch_slice<128, 64>(a, p.slices, p.pieces, nblocks, stream, ev0, ev1);
     }
     if (heads_kernel_shape(d)) return launch_wide(a, wide_groups(a.groups), stream, ev0, ev1);
     if (d.latent_dim == 320) return launch_mfma<320, 64>(a, nblocks, stream, ev0, ev1);
@@ -549,15 +555,16 @@ eg_mla_status run_decode(const eg_mla_dims& d, const DecodePlan& p, int32_t batc
   int64_t* sched_hdr = nullptr;
   int2* wg_start = nullptr;
   int2* seq_rows = nullptr;
-  if (p.balanced) {
-    // 0. balanced schedule of the head-split kernel (token ranges per work-group)
+  if (p.balanced || p.tok_balanced) {
+    // 0. balanced schedule (token ranges per work-group)
     // (computed by the absorption launch below)
     sched_hdr = reinterpret_cast<int64_t*>(ws + p.off_sched);
     wg_start = reinterpret_cast<int2*>(ws + p.off_sched + 16);
-    seq_rows = reinterpret_cast<int2*>(ws + p.off_sched + 16 + kWideMaxGroups * 8);
+    seq_rows = reinterpret_cast<int2*>(ws + p.off_sched + 16 + (p.balanced ? kWideMaxGroups * 8 : p.pieces * 16));
   }
-  const WideSchedArgs sched{seq_lens, p.capacity, p.balanced ? wide_groups(p.head_groups) : 0, sched_hdr, wg_start,
-                            seq_rows};
+  int4* tok_pieces = reinterpret_cast<int4*>(wg_start);
+  const SchedArgs sched{{seq_lens, p.capacity, p.balanced ? wide_groups(p.head_groups) : 0, sched_hdr, wg_start, seq_rows},
+                        {seq_lens, p.capacity, p.pieces, tok_pieces, seq_rows}};
   // 1. absorption (or inside the split kernel)
   if (!p.fused_absorb && !p.one_launch) {
     dim3 grid(d.num_heads, (d.latent_dim + kAbsorbCols - 1) / kAbsorbCols, (batch + kAbsorbRows - 1) / kAbsorbRows);
@@ -581,6 +588,17 @@ eg_mla_status run_decode(const eg_mla_dims& d, const DecodePlan& p, int32_t batc
         hipLaunchKernelGGL((absorb_mfma_kernel<128, kAbsBlocks, kAbsCols, true>), dim3(ga.x + 1, ga.y, ga.z),
                            dim3(256), 0, stream, q16, wuk16, qfull, batch, d.num_heads, d.latent_dim, d.rope_dim,
                            sched);
+      else if (p.tok_balanced && grouped)
+        hipLaunchKernelGGL((absorb_mfma_kernel<128, kAbsBlocks, kAbsCols, false, true>), dim3(ga.x + 1, ga.y, ga.z),
+                           dim3(256), 0, stream, q16, wuk16, qfull, batch, d.num_heads, d.latent_dim, d.rope_dim,
+                           sched);
+      else if (p.tok_balanced && narrow)
+        hipLaunchKernelGGL((absorb_mfma_kernel<128, 1, kAbsColsNarrow, false, true>), dim3(ga.x + 1, ga.y, ga.z),
+                           dim3(256), 0, stream, q16, wuk16, qfull, batch, d.num_heads, d.latent_dim, d.rope_dim,
+                           sched);
+      else if (p.tok_balanced)
+        hipLaunchKernelGGL((absorb_mfma_kernel<128, 1, kAbsCols, false, true>), dim3(ga.x + 1, ga.y, ga.z), dim3(256),
+                           0, stream, q16, wuk16, qfull, batch, d.num_heads, d.latent_dim, d.rope_dim, sched);
       else if (d.head_dim == 64) {
         if (narrow)
           hipLaunchKernelGGL((absorb_mfma_kernel<64, 1, kAbsColsNarrow>), ga, dim3(256), 0, stream, q16, wuk16, qfull,
@@ -621,6 +639,7 @@ eg_mla_status run_decode(const eg_mla_dims& d, const DecodePlan& p, int32_t batc
     a.part_o = part_o;
     a.sched_hdr = sched_hdr;
     a.wg_start = wg_start;
+    a.tok_pieces = tok_pieces;
     a.num_slots = num_slots;
     a.B = batch;
     a.H = d.num_heads;
@@ -665,7 +684,7 @@ eg_mla_status run_decode(const eg_mla_dims& d, const DecodePlan& p, int32_t batc
   // 3. combine + W_UV
   {
     dim3 grid(d.num_heads, batch);
-    const size_t lds = sizeof(float) * (d.latent_dim + (p.balanced ? static_cast<size_t>(kWideMaxGroups)
+    const size_t lds = sizeof(float) * (d.latent_dim + (p.balanced || p.tok_balanced ? static_cast<size_t>(std::max(kWideMaxGroups, p.pieces))
                                                                     : static_cast<size_t>(p.s_max) * p.slices));
     if (lds > 160 * 1024) return EG_MLA_ERR_UNSUPPORTED;
     const bool mfma_comb = bf && d.v_head_dim == 128 &&

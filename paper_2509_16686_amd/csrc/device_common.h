@@ -222,6 +222,15 @@ __device__ __forceinline__ int xcd_logical_block(int bid, int nblocks) {
   return xcd * per + min(xcd, rem) + local;
 }
 
+// Work-group id -> (token range, head block): with `groups` head blocks and
+// G ranges (G a multiple of 8), block ids 8 apart share an XCD, so the head
+// blocks of range g are block ids 8 (groups (g / 8) + hb) + g % 8.
+__device__ __forceinline__ void wide_block(int bid, int groups, int& range, int& hb) {
+  const int xcd = bid & 7, j = bid >> 3;
+  hb = j % groups;
+  range = (j / groups) * 8 + xcd;
+}
+
 // Cache row of token j given its page-table entry, clamped into the cache.
 __device__ __forceinline__ int64_t paged_slot(int page, int j, int P, int64_t num_slots) {
   const int64_t npages = num_slots / P;

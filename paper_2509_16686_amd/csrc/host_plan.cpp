@@ -12,6 +12,14 @@ constexpr int kTargetWorkItems = 1024;
 // Token-split MFMA kernel: one 4-wave work-group per compute unit streams
 // longest without gaps between its loads (256 compute units).
 constexpr int kTargetWorkItemsTok = 256;
+// ... and its smallest automatic split, one unit for each of its four waves
+// (measured with few sequences: 8 of 203 to 2000 tokens 14.9 us per call with
+// 64-token splits, 16.9 with 256), while the partials of a sequence stay few
+// (1 x 32768: 18.7 us with 128 partials, 19.8 with 256).
+constexpr int kMaxPartialsTok = 128;
+constexpr int kMinSplitTok = 64;
+// Smallest capacity for which the d_c 128 kernel takes the balanced schedule.
+constexpr int kTokBalancedMinCap = 1024;
 // fp32 matrix-core kernel: 4-wave work-groups, two per compute unit up to
 // d_c 64; above, a work-group's LDS leaves room for one (measured at batch 32,
 // d_c 256, lengths to 3003: 384-token splits 42.0 us per call, 192-token 48.7).
@@ -107,8 +115,11 @@ eg_mla_status make_decode_plan(const eg_mla_dims& d, int32_t batch, int32_t max_
     int64_t s = (work + target - 1) / target;
     const int gran = p.slices > 1 ? 256 : kTile;  // sliced kernel: whole 256-position scan rows
     s = (s + gran - 1) / gran * gran;
-    const int min_split = p.path == EG_MLA_PATH_MFMA || p.f32_mfma ? 256 : 128;
+    const int min_split = sliced_kernel && p.slices == 1 ? kMinSplitTok
+                          : p.path == EG_MLA_PATH_MFMA || p.f32_mfma ? 256
+                                                                     : 128;
     s = std::max<int64_t>(s, min_split);
+    if (sliced_kernel && p.slices == 1) s = std::max<int64_t>(s, (p.capacity / kMaxPartialsTok + kTile - 1) / kTile * kTile);
     s = std::min<int64_t>(s, max_split);
     split = static_cast<int>(s);
   }
@@ -130,20 +141,6 @@ eg_mla_status make_decode_plan(const eg_mla_dims& d, int32_t batch, int32_t max_
   const size_t B = static_cast<size_t>(std::max(batch, 0));
   const size_t H = static_cast<size_t>(d.num_heads);
   const size_t DQ = static_cast<size_t>(d.latent_dim + d.rope_dim);
-  const size_t rows = p.balanced ? kWideMaxGroups + B
-                                 : B * static_cast<size_t>(p.s_max) * static_cast<size_t>(p.slices);
-  size_t off = 0;
-  p.off_q = off;
-  off = align_up(off + B * H * DQ * 4);
-  p.off_ml = off;
-  off = align_up(off + rows * H * 2 * 4);
-  // partial outputs: fp32 sums, or (balanced schedule) fp16 rows normalised by their sums
-  p.off_o = off;
-  off = align_up(off + rows * H * static_cast<size_t>(d.latent_dim) * (p.balanced ? 2 : 4));
-  if (p.balanced) {
-    p.off_sched = off;
-    off = align_up(off + 16 + kWideMaxGroups * 8 + B * 8);
-  }
   // The split kernel absorbs the query itself when that costs each work-group
   // at most 2 heads' W_UK (8 to 16 splits per sequence, every split a
   // producer) and every work-group is resident at once (2 per compute unit);
@@ -154,9 +151,51 @@ eg_mla_status make_decode_plan(const eg_mla_dims& d, int32_t batch, int32_t max_
   const int64_t nblk = static_cast<int64_t>(std::max(batch, 0)) * p.s_max * p.head_groups;
   p.fused_absorb = sliced_kernel && p.slices == 1 && d.head_dim == 128 && p.s_max >= 8 && p.s_max <= 16 &&
                    nblk <= 2 * kTargetWorkItemsTok;
-  if (p.fused_absorb) {
-    p.off_flags = off;
-    off = align_up(off + B * static_cast<size_t>(p.head_groups) * static_cast<size_t>(p.s_max) * 8);
+  auto layout = [&]() {
+    const size_t rows = p.balanced       ? kWideMaxGroups + B
+                        : p.tok_balanced ? static_cast<size_t>(p.pieces)
+                                         : B * static_cast<size_t>(p.s_max) * static_cast<size_t>(p.slices);
+    size_t off = 0;
+    p.off_q = off;
+    off = align_up(off + B * H * DQ * 4);
+    p.off_ml = off;
+    off = align_up(off + rows * H * 2 * 4);
+    // partial outputs: fp32 sums, or (wide kernel) fp16 rows normalised by their sums
+    p.off_o = off;
+    off = align_up(off + rows * H * static_cast<size_t>(d.latent_dim) * (p.balanced ? 2 : 4));
+    if (p.balanced || p.tok_balanced) {
+      p.off_sched = off;
+      off = align_up(off + 16 + (p.balanced ? kWideMaxGroups * 8 : static_cast<size_t>(p.pieces) * 16) + B * 8);
+    }
+    if (p.fused_absorb) {
+      p.off_flags = off;
+      off = align_up(off + B * static_cast<size_t>(p.head_groups) * static_cast<size_t>(p.s_max) * 8);
+    }
+    return off;
+  };
+  size_t off = layout();
+  // Few splits per sequence: a work-group's time follows its sequence's
+  // length, so the d_c 128 kernel takes the balanced schedule, two
+  // work-groups per compute unit.  Not beyond the batch where the dispatcher
+  // itself evens out the work-groups, nor where a range could outgrow the
+  // token list, nor where the extra partial rows would take a call that fits
+  // the workspace-free entry's scratch out of it.
+  if (sliced_kernel && p.slices == 1 && !p.fused_absorb && d.head_dim == 128 && p.s_max < 8 &&
+      (plan == nullptr || plan->split_tokens == 0) && p.capacity >= kTokBalancedMinCap &&
+      batch <= kTokMaxBatch) {
+    const int pieces = kTokMaxPieces / p.head_groups / 8 * 8;
+    if (pieces > batch &&
+        static_cast<int64_t>(batch) * p.capacity / (pieces - batch) < kMaxSliceSplitTokens - 128) {
+      const size_t plain = off;
+      p.tok_balanced = true;
+      p.pieces = pieces;
+      off = layout();
+      if (off > plain && off > EG_MLA_NOALLOC_SCRATCH_BYTES && plain <= EG_MLA_NOALLOC_SCRATCH_BYTES) {
+        p.tok_balanced = false;
+        p.pieces = 0;
+        off = layout();
+      }
+    }
   }
   p.bytes = std::max<size_t>(off, kAlign);
   *out = p;

@@ -41,6 +41,11 @@ constexpr int kOneMaxLatent = 128;
 // (one work-group per range and block of 64 heads, one per compute unit of the
 // device over all head blocks).
 constexpr int kWideMaxGroups = 512;
+// Balanced schedule of the d_c 128 kernel: pieces (over all head groups),
+// sequences, and tokens of the smallest piece (four units for each wave).
+constexpr int kTokMaxPieces = 512;
+constexpr int kTokMaxBatch = 384;
+constexpr int kTokPieceMin = 256;
 
 struct DecodePlan {
   int path = EG_MLA_PATH_VALU;  // resolved: VALU or MFMA
@@ -53,14 +58,17 @@ struct DecodePlan {
   bool balanced = false;        // head-split kernel: balanced schedule (split_tokens = list chunk)
   bool f32_mfma = false;        // VALU-path shape served by the fp32 matrix-core kernel (split_f32.h)
   bool one_launch = false;      // ... in its single-launch form (absorption and up-projection inside)
+  bool tok_balanced = false;    // d_c 128 split kernel on the balanced schedule (at most `pieces` pieces)
+  int pieces = 0;
   bool fused_absorb = false;    // d_c 128 split kernel absorbs the query itself (no id slices, d_h 128)
   // workspace layout (byte offsets)
   size_t off_q = 0;     // fp32 [B, H, d_c + d_r]  absorbed query | RoPE query
   size_t off_ml = 0;    // fp32 [rows, H, 2]   running max (log2 domain), sum
   size_t off_o = 0;     // fp32 [rows, H, d_c] unnormalised latent outputs
-  size_t off_sched = 0; // balanced schedule: int64 [2] header, int2 [kWideMaxGroups] starts, int2 [B] rows
+  size_t off_sched = 0; // balanced schedule: int64 [2] header, int2 [kWideMaxGroups] starts
+                        // (d_c 128: int4 [pieces]), int2 [B] rows
   size_t off_flags = 0; // fused absorption: uint64 [B, head_groups, s_max] stamps
-  size_t bytes = 0;     // rows: B * s_max * slices, or kWideMaxGroups + B when balanced
+  size_t bytes = 0;     // rows: B * s_max * slices, or kWideMaxGroups + B, or `pieces`, when balanced
 };
 
 eg_mla_status check_dims(const eg_mla_dims* d);

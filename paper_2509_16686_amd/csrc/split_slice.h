@@ -175,18 +175,151 @@ __device__ __forceinline__ void absorb_head_128(const SplitArgs& a, int b, int h
   absorb_finish(a, b, h, r, red);
 }
 
-// FUSED (no id slices, d_h = 128): the work-groups of a sequence also absorb
-// its query.  Split s of the ns non-empty splits of sequence b absorbs the heads
-// j (of its group of 16) with j = s mod ns: their W_UK rows load with the page
-// table entries, the products are formed and stored device-coherently
-// before the token ids are loaded, and once the ids are in (vector memory
-// operations complete in issue order, so the stores are then complete) the
-// work-group publishes the call's stamp in qflags[b][group][s].  Before its first scores a work-group waits for the
-// stamps of splits 0 .. min(ns, 16) - 1 (the other work-groups of the
-// sequence run at the same time: one work-group per compute unit), polling at
-// most spin_limit times; if one is missing it absorbs all 16 heads itself
-// (the same bits), so the wait always ends.
-template <int DC, int DR, int NW, int D, int SL, bool FUSED = false>
+// FUSED (no id slices, d_h = 128, 8 to 16 splits per sequence): the
+// work-groups of a sequence also absorb its query.  Split s of the s_max splits
+// of sequence b absorbs the heads j (of its group of 16) with j = s mod s_max,
+// whether or not it holds tokens (with the heads spread over the non-empty
+// splits only, the one split of a short sequence absorbed all 16 in turn: the
+// whole call 27.5 against 16.9 us for 8 sequences of 203 to 2000 tokens in
+// 256-token splits): their W_UK rows load
+// with the page table entries, the products are formed and stored
+// device-coherently before the token ids are loaded, and once the ids are in
+// (vector memory operations complete in issue order, so the stores are then
+// complete) the work-group publishes the call's stamp in qflags[b][group][s];
+// an empty split then ends.  Before its first scores a work-group waits for
+// the stamps of all s_max splits (they run at the same time: at most two
+// work-groups per compute unit), polling at most spin_limit times; if one is
+// missing it absorbs all 16 heads itself (the same bits), so the wait always
+// ends.
+constexpr int kFusedHeads = 2;  // heads per split: s_max >= 8
+__device__ __forceinline__ void absorb_own_heads(const SplitArgs& a, int b, int hg, int s, float* red) {
+  AbsorbRegs pre[kFusedHeads];
+#pragma unroll
+  for (int i = 0; i < kFusedHeads; ++i)
+    if (s + i * a.s_max < 16) absorb_load(a, b, hg * 16 + s + i * a.s_max, pre[i]);
+#pragma unroll
+  for (int i = 0; i < kFusedHeads; ++i)
+    if (s + i * a.s_max < 16) absorb_finish(a, b, hg * 16 + s + i * a.s_max, pre[i], red);
+}
+__device__ __forceinline__ void publish_stamp(const SplitArgs& a, int b, int hg, int s) {
+  __hip_atomic_store(a.qflags + (static_cast<int64_t>(b) * a.groups + hg) * a.s_max + s, a.stamp, __ATOMIC_RELAXED,
+                     __HIP_MEMORY_SCOPE_AGENT);
+}
+// BAL (no id slices, not FUSED): items from a balanced schedule instead of
+// (sequence, split).  With the split size chosen from the capacity, a large
+// batch has one or a few items per sequence and the longest sequences set the
+// time.  Here every sequence is cut into the fewest equal pieces of at most c
+// tokens, c the smallest (to a step of the search) that makes at most G
+// pieces: work-group (piece, head group) handles one piece, all of them about
+// the same size whatever the length mix, and writes its partial at row
+// `piece`.  (Ranges of equal length across sequence boundaries, as the wide
+// kernel takes, measured slower: a range over two sequences pays the list,
+// first loads and merge twice in turn.)  256 sequences of 250 to 3901 tokens:
+// the kernel 72.5 -> 56 us; 48 of 250 to 4096: the call 34.1 -> 27.7 us.  The
+// schedule itself adds 1.5 us to the absorption launch, which a batch of equal
+// lengths pays for nothing (64 x 2048: 25.7 -> 27.4 us).
+// tok_schedule, run by one more work-group of the absorption launch, writes
+// each piece as (sequence, first token, tokens, 0) and each sequence's (first
+// row, rows).
+struct TokSchedArgs {
+  const int32_t* seq_lens;
+  int cap, G;
+  int4* pieces;    // [G]
+  int2* seq_rows;  // [B]
+};
+
+template <int NT>
+__device__ __forceinline__ void tok_schedule(const TokSchedArgs& sa, int B) {
+  static_assert(NT == 256, "64 candidates x 4 quarters of the batch");
+  __shared__ int len[kTokMaxBatch];
+  __shared__ int pre[kTokMaxBatch + 1];  // pieces before sequence b
+  __shared__ int wsum[NT / 64];
+  __shared__ int cnt[NT];
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  int v = 0;
+  for (int b = tid; b < B; b += NT) {
+    const int L = clamp_len(sa.seq_lens[b], sa.cap);
+    len[b] = L;
+    v += L;
+  }
+#pragma unroll
+  for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o, 64);
+  if (lane == 0) wsum[w] = v;
+  __syncthreads();
+  const int N = wsum[0] + wsum[1] + wsum[2] + wsum[3];
+  // candidate piece sizes, multiples of 16: from N / G, below which there
+  // are always more than G pieces, to N / (G - B), which always fits (B < G)
+  const int lo = max(kTokPieceMin, (N / sa.G + 15) & ~15), hi = max(lo, (N / (sa.G - B) + 16) & ~15);
+  const int step = ((hi - lo) / 62 + 16) & ~15;
+  // ceil(L / c), exact for lengths below 2^24
+  auto pieces_of = [](int L, int c, float rc) {
+    const int x = L + c - 1;
+    const int q = static_cast<int>(static_cast<float>(x) * rc);
+    const int r = x - q * c;
+    return q + (r >= c ? 1 : 0) - (r < 0 ? 1 : 0);
+  };
+  // one more candidate (the last lane): a tenth above an even cut into G / 2
+  // pieces; where it makes at most that many, one work-group per compute unit
+  // starts, loads and merges half as often
+  const int half = sa.G / 2;
+  const int even = max(kTokPieceMin, (N / half + N / (10 * half) + 15) & ~15);
+  {
+    const int c = lane == 63 ? even : lo + step * lane;
+    const float rc = 1.f / static_cast<float>(c);
+    int k = 0;
+#pragma unroll 8
+    for (int b = w; b < B; b += 4) k += pieces_of(len[b], c, rc);
+    cnt[tid] = k;
+  }
+  __syncthreads();
+  const int total = cnt[lane] + cnt[64 + lane] + cnt[128 + lane] + cnt[192 + lane];
+  const uint64_t fits = __builtin_amdgcn_ballot_w64(total <= (lane == 63 ? half : sa.G));
+  const int c = (fits >> 63) ? even : lo + step * (fits ? __builtin_ctzll(fits) : 62);
+  const float rc = 1.f / static_cast<float>(c);
+  int carry = 0;
+  for (int base = 0; base < B; base += NT) {
+    const int b = base + tid;
+    const int k = b < B ? pieces_of(len[b], c, rc) : 0;
+    int x = k;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const int y = __shfl_up(x, o, 64);
+      if (lane >= o) x += y;
+    }
+    __syncthreads();
+    if (lane == 63) wsum[w] = x;
+    __syncthreads();
+    int before = carry;
+#pragma unroll
+    for (int i = 0; i < NT / 64; ++i) {
+      if (i < w) before += wsum[i];
+      carry += wsum[i];
+    }
+    if (b < B) {
+      pre[b] = before + x - k;
+      sa.seq_rows[b] = make_int2(before + x - k, k);
+    }
+  }
+  __syncthreads();
+  for (int g = tid; g < sa.G; g += NT) {
+    int4 r = make_int4(0, 0, 0, 0);  // no tokens
+    if (g < carry) {
+      int l = 0, h = B;  // the last sequence whose first piece is at most g (empty ones have no piece)
+      while (h - l > 1) {
+        const int mid = (l + h) >> 1;
+        if (pre[mid] <= g) l = mid;
+        else h = mid;
+      }
+      const int L = len[l], k = pieces_of(L, c, rc);
+      const int size = ((L + k - 1) / k + 15) & ~15;  // at most c, so that the k - 1 first pieces stay below L
+      const int t0 = (g - pre[l]) * size;
+      r = make_int4(l, t0, min(size, L - t0), 0);
+    }
+    sa.pieces[g] = r;
+  }
+}
+
+template <int DC, int DR, int NW, int D, int SL, bool FUSED = false, bool BAL = false>
 __global__ __launch_bounds__(NW * 64, 2) void split_slice_kernel(SplitArgs a) {
   using Cfg = SsplitCfg<DC, DR, NW>;
   constexpr int NC = Cfg::NC, NR = Cfg::NR, NB = Cfg::NB, DQ = Cfg::DQ, TS = Cfg::TS;
@@ -205,16 +338,32 @@ __global__ __launch_bounds__(NW * 64, 2) void split_slice_kernel(SplitArgs a) {
   // work-group x runs slice x % SL (its XCD); the rest is the (b, s, group) item
   const int k = SL > 1 ? static_cast<int>(blockIdx.x % SL) : 0;
   const int item = SL > 1 ? static_cast<int>(blockIdx.x / SL) : xcd_logical_block(blockIdx.x, gridDim.x);
-  const int hg = item % a.groups;
-  const int s = (item / a.groups) % a.s_max;
-  const int b = item / (a.groups * a.s_max);
-  const int t0 = s * a.split;
-  const int L = clamp_len(a.seq_lens[b], a.cap);
-  if (t0 >= L) return;  // empty split: the merge reads no partial of it (uniform over the work-group)
-  const int n = min(t0 + a.split, L) - t0;
-
+  int hg = item % a.groups, s = (item / a.groups) % a.s_max, b = item / (a.groups * a.s_max), t0 = s * a.split;
+  int n, piece = 0, L = 0;
+  if constexpr (BAL) {
+    wide_block(blockIdx.x, a.groups, piece, hg);
+    const int4 r = a.tok_pieces[piece];
+    b = r.x;
+    t0 = r.y;
+    n = r.z;
+    if (n <= 0) return;
+  } else {
+    L = clamp_len(a.seq_lens[b], a.cap);
+    n = min(a.split, L - t0);
+  }
   const int tid = threadIdx.x, lane = tid & 63, r16 = lane & 15, g = lane >> 4;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  if (n <= 0) {  // empty split: the merge reads no partial of it (uniform over the work-group)
+    if constexpr (FUSED) {
+      if (L > 0) {  // its heads are still its own to absorb
+        absorb_own_heads(a, b, hg, s, reinterpret_cast<float*>(lds));
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();
+        if (tid == 0) publish_stamp(a, b, hg, s);
+      }
+    }
+    return;
+  }
 
   const uint16_t* __restrict__ cache = static_cast<const uint16_t*>(a.cache);
   const uint16_t* __restrict__ gate = static_cast<const uint16_t*>(a.gate);
@@ -281,22 +430,19 @@ __global__ __launch_bounds__(NW * 64, 2) void split_slice_kernel(SplitArgs a) {
     int pp[PER], psl[PER], pid[PER];
 #pragma unroll
     for (int e = 0; e < PER; ++e) pp[e] = min(tid + e * NW * 64, n - 1);
-    // FUSED: this split's heads j = s, s + ns, ... < 16 of the group; the
-    // W_UK rows of the first two load together with the page table entries
-    const int ns = (L + a.split - 1) / a.split;  // non-empty splits of sequence b (s < ns)
-    AbsorbRegs pre[FUSED ? 2 : 1];
+    // FUSED: the W_UK rows of this split's heads load together with the page table entries
+    AbsorbRegs pre[FUSED ? kFusedHeads : 1];
     if constexpr (FUSED) {
 #pragma unroll
-      for (int i = 0; i < 2; ++i)
-        if (s + i * ns < 16) absorb_load(a, b, hg * 16 + s + i * ns, pre[i]);
+      for (int i = 0; i < kFusedHeads; ++i)
+        if (s + i * a.s_max < 16) absorb_load(a, b, hg * 16 + s + i * a.s_max, pre[i]);
     }
     split_slots(a, b, t0, pp, psl, nper);
     if constexpr (FUSED) {
       // (the LDS list is written after this)
 #pragma unroll
-      for (int i = 0; i < 2; ++i)
-        if (s + i * ns < 16) absorb_finish(a, b, hg * 16 + s + i * ns, pre[i], reinterpret_cast<float*>(lds));
-      for (int j = s + 2 * ns; j < 16; j += ns) absorb_head_128(a, b, hg * 16 + j, reinterpret_cast<float*>(lds));
+      for (int i = 0; i < kFusedHeads; ++i)
+        if (s + i * a.s_max < 16) absorb_finish(a, b, hg * 16 + s + i * a.s_max, pre[i], reinterpret_cast<float*>(lds));
       __atomic_signal_fence(__ATOMIC_SEQ_CST);  // the stores above are issued before the loads below
     }
 #pragma unroll
@@ -324,16 +470,12 @@ __global__ __launch_bounds__(NW * 64, 2) void split_slice_kernel(SplitArgs a) {
     }
     ntok = n;
     if constexpr (FUSED) {
-      if (s < 16) {
-        // Only the first rows' D * NRL loads, issued last, may still be in
-        // flight: this thread's absorbed stores, issued before its ids, are
-        // complete.  Then the stamp goes out.
-        asm volatile("s_waitcnt vmcnt(%0)" ::"n"(D * NRL) : "memory");
-        __syncthreads();
-        if (tid == 0)
-          __hip_atomic_store(a.qflags + (static_cast<int64_t>(b) * a.groups + hg) * a.s_max + s, a.stamp,
-                             __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      }
+      // Only the first rows' D * NRL loads, issued last, may still be in
+      // flight: this thread's absorbed stores, issued before its ids, are
+      // complete.  Then the stamp goes out.
+      asm volatile("s_waitcnt vmcnt(%0)" ::"n"(D * NRL) : "memory");
+      __syncthreads();
+      if (tid == 0) publish_stamp(a, b, hg, s);
     }
   } else {
     // ---- phase 1a: slots and ids of this wave's scan rows (all loads first) ----
@@ -422,8 +564,7 @@ __global__ __launch_bounds__(NW * 64, 2) void split_slice_kernel(SplitArgs a) {
   bf16x8_t qr[NR > 0 ? NR : 1];
   if constexpr (FUSED) {
     __syncthreads();  // the list is complete (and the absorption's LDS is free)
-    const int ns = (L + a.split - 1) / a.split;
-    const int np = min(ns, 16);
+    const int np = a.s_max;  // producers (at most 16): every split of the sequence, empty or not
     int* okp = reinterpret_cast<int*>(mbuf);
     if (w == 0) {
       const unsigned long long* fl = a.qflags + (static_cast<int64_t>(b) * a.groups + hg) * a.s_max;
@@ -594,7 +735,8 @@ __global__ __launch_bounds__(NW * 64, 2) void split_slice_kernel(SplitArgs a) {
   // ---- phase 3: merge the waves' partial results; write the work item's partial ----
   l_run += __shfl_xor(l_run, 16, 64);
   l_run += __shfl_xor(l_run, 32, 64);
-  const int64_t pbase = ((static_cast<int64_t>(b) * a.s_max + s) * SL + k) * a.H + hg * 16;
+  const int64_t pbase = (BAL ? static_cast<int64_t>(piece)
+                             : (static_cast<int64_t>(b) * a.s_max + s) * SL + k) * a.H + hg * 16;
   if (g == 0) mbuf[w * 16 + r16] = m_run;
   __syncthreads();  // also: every wave is done with the list and its tile (obuf aliases them)
   float M = -INFINITY;

@@ -190,15 +190,6 @@ __device__ __forceinline__ void wide_schedule(const WideSchedArgs& sa, int B) {
   }
 }
 
-// Work-group id -> (token range, head block): with `groups` head blocks and
-// G ranges (G a multiple of 8), block ids 8 apart share an XCD, so the head
-// blocks of range g are block ids 8 (groups (g / 8) + hb) + g % 8.
-__device__ __forceinline__ void wide_block(int bid, int groups, int& range, int& hb) {
-  const int xcd = bid & 7, j = bid >> 3;
-  hb = j % groups;
-  range = (j / groups) * 8 + xcd;
-}
-
 // Walks this work-group's segments (its range's part of one sequence each)
 // and their list chunks: seg_begin(b) before the first chunk of sequence b's
 // segment, chunk(n, nunits) once the chunk's token list (n tokens, padded to

@@ -1,0 +1,79 @@
+"""The d_c 128 decode's work distribution: the balanced schedule of larger batches, short splits and the shared
+absorption of small ones."""
+import numpy as np
+import pytest
+
+from paper_2509_16686_amd import binding as B
+from paper_2509_16686_amd import workloads as W
+from parity import assert_close, oracle_decode, say
+
+
+def decode(inp, plan=None):
+    import torch
+    dd = B.stage_decode(inp)
+    B.run_decode(dd, plan=plan)
+    torch.cuda.synchronize()
+    return B.out_to_f64(dd.out)
+
+
+def lens_mix(batch, top, seed):
+    """Empty, single-token, unit-edge and piece-edge lengths among random ones, one sequence at the top."""
+    lens = np.random.default_rng(seed).integers(1, top // 4, batch)
+    edges = [0, 1, 16, 17, 255, 256, 257, 512, 513, 0]
+    lens[:len(edges)] = edges
+    lens[-1] = top
+    return lens.astype(np.int32)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("batch,heads,top", [
+    (33, 16, 1024),    # the smallest balanced batch and capacity
+    (40, 32, 4100),    # two head groups share each piece
+    (64, 16, 9000),    # one long sequence: pieces of the search's upper end
+    (384, 16, 1100),   # the largest balanced batch
+    (385, 16, 1100),   # past it: one item per sequence
+])
+def test_balanced_schedule(gpu, batch, heads, top):
+    wl = W.WORKLOADS[1].replace(name="balanced", batch=batch, heads=heads, vocab=3000, seq_len=None,
+                                seq_len_range=(0, top), page_size=16, paged=True, seed=5)
+    inp = W.generate(wl, seq_lens=lens_mix(batch, top, batch))
+    say(f"decode balanced B={batch} H={heads} top={top}")
+    got = decode(inp)
+    assert_close(got, oracle_decode(inp), "bf16", "balanced")
+    assert not got[inp.seq_lens == 0].any()
+    # all of one length: every sequence the same number of pieces
+    inp = W.generate(wl, seq_lens=np.full(batch, 1024, dtype=np.int32))
+    got = decode(inp)
+    d = got - decode(inp, B.make_plan(B.PATH_MFMA, 256))  # (sequence, split) items
+    assert np.linalg.norm(d) <= 5e-3 * np.linalg.norm(got)  # two bf16 outputs of sums in another order
+
+
+@pytest.mark.gpu
+def test_balanced_schedule_no_tokens(gpu):
+    wl = W.WORKLOADS[1].replace(batch=40, vocab=100, seq_len=None, seq_len_range=(0, 1024), page_size=64, paged=True)
+    inp = W.generate(wl, seq_lens=np.zeros(40, dtype=np.int32))
+    assert not decode(inp).any()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("lens", [[1, 64, 65, 0, 129, 2000], [3, 300], [16384]])
+def test_short_splits(gpu, lens):
+    """Few sequences: 64-token splits, most of them empty for the short ones."""
+    wl = W.WORKLOADS[1].replace(batch=len(lens), vocab=500, seq_len=None, seq_len_range=(0, max(lens)), page_size=16,
+                                paged=True, seed=6)
+    inp = W.generate(wl, seq_lens=np.array(lens, dtype=np.int32))
+    say(f"decode short splits {lens}")
+    assert_close(decode(inp), oracle_decode(inp), "bf16", f"short splits {lens}")
+
+
+def test_balanced_workspace_fits_the_scratch_as_before():
+    """A batch whose (sequence, split) plan fits the 32 MiB scratch fits it with the plan it gets."""
+    d = B.make_dims(num_heads=16, head_dim=128, v_head_dim=128, latent_dim=128, rope_dim=64, vocab_size=50304)
+    rows = lambda b, r: b * 16 * 192 * 4 + r * 16 * 130 * 4
+    for b in list(range(1, 400, 7)) + [1000, 1500]:
+        for pages in (1, 4, 16, 40, 64, 200, 512, 2048):
+            cap = 64 * pages
+            split = min(4096, max(256, -(-(b * cap // 256) // 32) * 32))
+            before = rows(b, b * -(-cap // split))
+            if before < (32 << 20) - 65536:
+                assert B.decode_workspace_size(d, b, pages) <= 32 << 20, (b, pages)
