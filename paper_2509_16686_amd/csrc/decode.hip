@@ -241,6 +241,7 @@ __global__ __launch_bounds__(kValuThreads) void split_valu_kernel(SplitArgs a) {
 #include "split_mfma.h"
 #include "split_slice.h"
 #include "split_wide.h"
+#include "split_rows.h"
 #include "split_f32.h"
 namespace egmla {
 
@@ -501,7 +502,10 @@ hipError_t launch_split(const eg_mla_dims& d, const DecodePlan& p, const SplitAr
       return launch_slice<128, 64>(a, p.slices, p.pieces, nblocks, stream, ev0, ev1);
     }
     if (heads_kernel_shape(d)) return launch_wide(a, wide_groups(a.groups), stream, ev0, ev1);
-    if (d.latent_dim == 320) return launch_mfma<320, 64>(a, nblocks, stream, ev0, ev1);
+    if (rows_kernel_shape(d)) {
+      hipExtLaunchKernelGGL((split_rows_kernel<320, 64, 4>), dim3(nblocks), dim3(256), 0, stream, ev0, ev1, 0, a);
+      return hipGetLastError();
+    }
     if (d.latent_dim == 512) return launch_mfma<512, 64>(a, nblocks, stream, ev0, ev1);
     return hipErrorInvalidValue;
   }

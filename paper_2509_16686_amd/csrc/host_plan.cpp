@@ -40,6 +40,7 @@ bool mfma_shape_supported(const eg_mla_dims& d) {
 }
 
 bool tok_kernel_shape(const eg_mla_dims& d) { return d.latent_dim == 128 && d.rope_dim == 64; }
+bool rows_kernel_shape(const eg_mla_dims& d) { return d.latent_dim == 320 && d.rope_dim == 64; }
 bool heads_kernel_shape(const eg_mla_dims& d) {
   return d.latent_dim == 512 && d.rope_dim == 64 && d.head_dim == 128 && d.v_head_dim == 128 &&
          d.num_heads % kHeadsPerItemWide == 0;
@@ -98,6 +99,9 @@ eg_mla_status make_decode_plan(const eg_mla_dims& d, int32_t batch, int32_t max_
   // automatic: no slices (measured faster on MI355X: a sliced work item must
   // resolve its token ids before its first cache-row load)
   p.slices = sliced_kernel && req_slices == kIdSlices ? kIdSlices : 1;
+  const bool rows_kernel = p.path == EG_MLA_PATH_MFMA && rows_kernel_shape(d);
+  // kernels whose waves own whole units of tokens take short splits
+  const bool unit_kernel = (sliced_kernel && p.slices == 1) || rows_kernel;
   const int max_split = sliced_kernel ? kMaxSliceSplitTokens : kMaxSplitTokens;
 
   int split = plan ? plan->split_tokens : 0;
@@ -110,16 +114,19 @@ eg_mla_status make_decode_plan(const eg_mla_dims& d, int32_t batch, int32_t max_
         static_cast<int64_t>(std::max(batch, 1)) * std::max(p.capacity, 1) * p.head_groups * p.slices;
     const int64_t target =
         p.path == EG_MLA_PATH_MFMA && (tok_kernel_shape(d) || heads_kernel_shape(d)) ? kTargetWorkItemsTok
+        // (measured: 256 x 2048 117 us per call against 122 with two work-groups
+        // per compute unit, 32 x 4096 42.5 against 47.9)
+        : rows_kernel ? kTargetWorkItemsTok
         : p.f32_mfma ? (d.latent_dim <= 64 ? kTargetWorkItemsF32 : kTargetWorkItemsF32 / 2)
                      : kTargetWorkItems;
     int64_t s = (work + target - 1) / target;
     const int gran = p.slices > 1 ? 256 : kTile;  // sliced kernel: whole 256-position scan rows
     s = (s + gran - 1) / gran * gran;
-    const int min_split = sliced_kernel && p.slices == 1 ? kMinSplitTok
+    const int min_split = unit_kernel ? kMinSplitTok
                           : p.path == EG_MLA_PATH_MFMA || p.f32_mfma ? 256
                                                                      : 128;
     s = std::max<int64_t>(s, min_split);
-    if (sliced_kernel && p.slices == 1) s = std::max<int64_t>(s, (p.capacity / kMaxPartialsTok + kTile - 1) / kTile * kTile);
+    if (unit_kernel) s = std::max<int64_t>(s, (p.capacity / kMaxPartialsTok + kTile - 1) / kTile * kTile);
     s = std::min<int64_t>(s, max_split);
     split = static_cast<int>(s);
   }
@@ -180,12 +187,12 @@ eg_mla_status make_decode_plan(const eg_mla_dims& d, int32_t batch, int32_t max_
   // itself evens out the work-groups, nor where a range could outgrow the
   // token list, nor where the extra partial rows would take a call that fits
   // the workspace-free entry's scratch out of it.
-  if (sliced_kernel && p.slices == 1 && !p.fused_absorb && d.head_dim == 128 && p.s_max < 8 &&
+  if (sliced_kernel && p.slices == 1 && !p.fused_absorb && d.head_dim == 128 && batch > 32 && p.s_max < 8 &&
       (plan == nullptr || plan->split_tokens == 0) && p.capacity >= kTokBalancedMinCap &&
       batch <= kTokMaxBatch) {
     const int pieces = kTokMaxPieces / p.head_groups / 8 * 8;
     if (pieces > batch &&
-        static_cast<int64_t>(batch) * p.capacity / (pieces - batch) < kMaxSliceSplitTokens - 128) {
+        static_cast<int64_t>(batch) * p.capacity / (pieces - batch) < max_split - 128) {
       const size_t plain = off;
       p.tok_balanced = true;
       p.pieces = pieces;

@@ -28,6 +28,8 @@ constexpr int kIdSlices = 8;
 bool mfma_shape_supported(const eg_mla_dims& d);
 // MFMA shapes served by the token-split kernel (16 heads per work item)...
 bool tok_kernel_shape(const eg_mla_dims& d);
+// ... by the whole-row kernel (wider latents, 16 heads per work item)...
+bool rows_kernel_shape(const eg_mla_dims& d);
 // ... and by the head-split kernel (64 heads per work item); the others by the
 // dimension-split kernel (16 heads per work item).
 bool heads_kernel_shape(const eg_mla_dims& d);
