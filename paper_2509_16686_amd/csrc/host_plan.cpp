@@ -341,7 +341,7 @@ eg_mla_status validate_prefill_varlen(const eg_mla_dims* d, int32_t batch, int32
 
 bool literal_tile_shape(const eg_mla_dims& d) {
   return d.dtype == EG_MLA_BF16 && d.latent_dim == 128 && d.head_dim == 128 && d.v_head_dim == 128 &&
-         d.rope_dim == 64 && d.num_heads <= 160 && literal_lds_bytes(d.num_heads) <= 160 * 1024;
+         d.rope_dim == 64 && d.num_heads <= 160 && literal_lds_bytes(d.num_heads, 1) <= 160 * 1024;
 }
 
 size_t literal_generic_lds_bytes(const eg_mla_dims& d) {
@@ -353,11 +353,16 @@ size_t literal_generic_lds_bytes(const eg_mla_dims& d) {
               H * static_cast<size_t>(d.v_head_dim));
 }
 
-size_t literal_lds_bytes(int num_heads) {
-  // weight / gate-tile region, per-wave scores [4][H][32], value sums [4][d_v],
-  // two sums per head, per-wave figures per head, token means [4][32] (all fp32)
-  return 272 * 256 + 4 * static_cast<size_t>(num_heads) * 32 * 4 + 4 * 128 * 4 +
-         static_cast<size_t>(num_heads) * (2 + 12) * 4 + 4 * 32 * 4;
+size_t literal_lds_bytes(int num_heads, int groups) {
+  // per head group: weight / gate-tile region, value sums [4][d_v] and, for two
+  // groups, the tokens' moments [3][4][32]; per-wave scores [4][H][32], two
+  // sums per head, per-wave figures per head, token means [4][32] (all fp32)
+  return static_cast<size_t>(groups) * (272 * 256 + 4 * 128 * 4 + (groups > 1 ? 3 * 4 * 32 * 4 : 0)) +
+         4 * static_cast<size_t>(num_heads) * 32 * 4 + static_cast<size_t>(num_heads) * (2 + 12) * 4 + 4 * 32 * 4;
+}
+
+int literal_head_groups(int num_heads) {
+  return num_heads % 2 == 0 && literal_lds_bytes(num_heads, 2) <= 160 * 1024 ? 2 : 1;
 }
 
 size_t literal_workspace_bytes(const eg_mla_dims& d, int32_t batch, int32_t max_pages_per_seq) {

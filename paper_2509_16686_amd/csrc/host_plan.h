@@ -126,7 +126,10 @@ eg_mla_status validate_prefill_varlen(const eg_mla_dims* d, int32_t batch, int32
 // layer takes the tile kernel (bf16, d_c = d_h = d_v = 128, d_r = 64, at most
 // 160 heads) or the generic one, and the generic kernel's LDS.
 size_t literal_workspace_bytes(const eg_mla_dims& d, int32_t batch, int32_t max_pages_per_seq);
-size_t literal_lds_bytes(int num_heads);
+size_t literal_lds_bytes(int num_heads, int groups);
+// Head groups of the tile kernel's work-group (4 waves each): two where the heads
+// split evenly and both weight regions fit the LDS, else one.
+int literal_head_groups(int num_heads);
 bool literal_tile_shape(const eg_mla_dims& d);
 size_t literal_generic_lds_bytes(const eg_mla_dims& d);
 eg_mla_status validate_literal(const eg_mla_dims* d, int32_t batch, const void* q, const void* latent_cache,

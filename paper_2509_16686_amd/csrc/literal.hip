@@ -18,7 +18,15 @@
 // value pass centres each x on its token's mean before weighting it.
 // Two kernels (bf16 storage, d_c = d_h = d_v = 128, d_r = 64):
 //  1. literal_tile_kernel: one work-group per (sequence, 128 cached tokens),
-//     4 waves of 32 tokens, split-K style.  Pass 1 walks the heads: one head's
+//     split-K style: G head groups of 4 waves of 32 tokens, each with its own
+//     heads, weight region and pivot; the groups meet once, to combine a
+//     token's moments.  The walk over the heads is a chain of stage, barrier
+//     and products that takes the same time for one tile as for 200 (110 us
+//     for 16 heads in one group), so two groups are taken wherever the LDS
+//     holds two weight regions: 8 sequences of 1000 to 4096 tokens 130 -> 90
+//     us, one of 64 tokens 111 -> 75, 32 of 2048 to 4096 460 -> 391 (there one
+//     group already runs two work-groups per compute unit; the gain is the
+//     wider gate loads, see lt_out_row).  Pass 1 walks the heads: one head's
 //     W_UK and W_UV rows are staged in LDS (coalesced, the next head's rows
 //     travel in registers meanwhile) and x = kv (.) g comes out of
 //     v_mfma_f32_32x32x16_bf16 with a token's outputs in its own lanes, so the
@@ -63,6 +71,11 @@ __device__ __forceinline__ u32x4_t ld_lane16(const uint16_t* base, uint32_t byte
   return *reinterpret_cast<const u32x4_t*>(reinterpret_cast<const unsigned char*>(base) + byte_off);
 }
 
+// LDS row, within its 32-output block, of W row d: an MFMA output lane of half
+// hf holds block rows 8 qq + 4 hf + e, which are the 16 adjacent outputs
+// 16 hf + 4 qq + e, so that its gate words come in two 16-byte loads
+__device__ __forceinline__ int lt_out_row(int d) { return (d & ~28) | (((d >> 2) & 3) << 3) | (((d >> 4) & 1) << 2); }
+
 __device__ __forceinline__ float lane_half_sum(float v) {
   // lanes l and l + 32 exchange and add (both end with the sum)
   const uint32_t u = __float_as_uint(v);
@@ -70,29 +83,34 @@ __device__ __forceinline__ float lane_half_sum(float v) {
   return __uint_as_float(s[0]) + __uint_as_float(s[1]);
 }
 
-template <bool LN, bool ADD>
-__global__ __launch_bounds__(256, 2) void literal_tile_kernel(
+template <bool LN, bool ADD, int G>
+__global__ __launch_bounds__(256 * G, 2) void literal_tile_kernel(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ cache, const int32_t* __restrict__ ids,
     const uint16_t* __restrict__ gate, const uint16_t* __restrict__ w_uk, const uint16_t* __restrict__ w_uv,
     const uint16_t* __restrict__ ln_w, const uint16_t* __restrict__ ln_b, const int32_t* __restrict__ seq_lens,
     const int32_t* __restrict__ page_table, int P, int max_pages, int64_t num_slots, int H, int V,
     float scale_log2, float* __restrict__ part) {
   extern __shared__ __attribute__((aligned(16))) unsigned char lt_lds[];
-  uint16_t* wsh = reinterpret_cast<uint16_t*>(lt_lds);        // region R
-  float* kd = reinterpret_cast<float*>(lt_lds + kLtRegion);    // [4 waves][H][32 tokens]: key dot, score, a_j
-  float* ob = kd + 4 * H * 32;                                 // [4][d_v] pass-2 sums; pass 1: q w of the head
-  float* sqw = ob + 4 * kLtDV;                                 // [H] sum_d q_d w_d
+  // head group of this wave (4 waves each), and the wave and thread within it
+  const int grp = G == 1 ? 0 : __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) >> 8);
+  const int Hn = H / G, h0 = grp * Hn;                         // the group's heads h0 .. h0 + Hn - 1
+  uint16_t* wsh = reinterpret_cast<uint16_t*>(lt_lds + grp * kLtRegion);  // the group's region R
+  float* kd = reinterpret_cast<float*>(lt_lds + G * kLtRegion);  // [4 waves][H][32 tokens]: key dot, score, a_j
+  float* obs = kd + 4 * H * 32;
+  float* ob = obs + grp * 4 * kLtDV;                           // [4][d_v] pass-2 sums; pass 1: q w of the head
+  float* sqw = obs + G * 4 * kLtDV;                            // [H] sum_d q_d w_d
   float* sqb = sqw + H;                                        // [H] sum_d q_d b_d
   float* wr = sqb + H;                                         // [2][4][H] per-wave max, sum p
   float* mus = wr + 12 * H;                                    // [4 waves][32 tokens] token means
+  float* mst = mus + 4 * 32;                                   // [G][K, m1, var][4 waves][32 tokens]
   // at least one head (the host checks): every head loop runs, so no load is
   // left pending on a zero-trip path into the loops after it
-  __builtin_assume(H >= 1);
+  __builtin_assume(H >= G);
   const int b = blockIdx.y, tile = blockIdx.x;
   const int L = clamp_len(seq_lens[b], P * max_pages);
   const int j0 = tile * 128;
   if (j0 >= L) return;  // whole work-group, before any barrier
-  const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, t = lane & 31, hf = lane >> 5;
+  const int all = threadIdx.x, tid = all & 255, w = tid >> 6, lane = tid & 63, t = lane & 31, hf = lane >> 5;
   const int j = j0 + 32 * w + t;
   const bool ok = j < L;  // positions past the sequence repeat its last token and get p = 0
   const int64_t row = cache_slot(page_table, b, min(j, L - 1), P, max_pages, num_slots);
@@ -123,7 +141,7 @@ __global__ __launch_bounds__(256, 2) void literal_tile_kernel(
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
       const int p = tid + 256 * i;
-      *reinterpret_cast<u32x4_t*>(wsh + (half * kLtDH + (p >> 4)) * kLtWRow + (p & 15) * 8) = ws[i];
+      *reinterpret_cast<u32x4_t*>(wsh + (half * kLtDH + lt_out_row(p >> 4)) * kLtWRow + (p & 15) * 8) = ws[i];
     }
   };
   uint32_t qn = 0, wn = 0;  // q and the LayerNorm weight at dim tid % 128 of the next head
@@ -134,27 +152,27 @@ __global__ __launch_bounds__(256, 2) void literal_tile_kernel(
   auto put_qa = [&]() {
     if (tid < kLtDH) ob[tid] = bf16_to_f32(static_cast<uint16_t>(qn)) * bf16_to_f32(static_cast<uint16_t>(wn));
   };
-  const uint16_t* grow = gate + static_cast<int64_t>(id) * width + 4 * hf;
-  u32x2_t gv[4][4];  // gate words of the block 4 ahead (ring slot = block % 4)
+  const uint16_t* grow = gate + static_cast<int64_t>(id) * width + 16 * hf;
+  u32x4_t gv[4][2];  // gate words of the block 4 ahead (ring slot = block % 4)
   auto fetch_g = [&](int head, int blk) {
 #pragma unroll
-    for (int qq = 0; qq < 4; ++qq)
-      gv[blk & 3][qq] = *reinterpret_cast<const u32x2_t*>(grow + head * kLtHeadW + 32 * blk + 8 * qq);
+    for (int i = 0; i < 2; ++i)
+      gv[blk & 3][i] = *reinterpret_cast<const u32x4_t*>(grow + head * kLtHeadW + 32 * blk + 8 * i);
   };
-  // issue order as in the loop (the V half's rows older than the 16 gate loads),
+  // issue order as in the loop (the V half's rows older than the 8 gate loads),
   // so the waits at the loop head stay partial on entry too
-  fetch_half(w_uk, 0);
-  fetch_qa(0);
+  fetch_half(w_uk, h0);
+  fetch_qa(h0);
   put_half(0);
   put_qa();
-  if (LN) fetch_half(w_uv, 0);
+  if (LN) fetch_half(w_uv, h0);
   __builtin_amdgcn_sched_barrier(0);  // keep that order
 #pragma unroll
-  for (int blk = 0; blk < 4; ++blk) fetch_g(0, blk);
+  for (int blk = 0; blk < 4; ++blk) fetch_g(h0, blk);
   __builtin_amdgcn_sched_barrier(0);
   if (LN) {
     // sum_d q_d w_d and sum_d q_d b_d of every head (a wave covers 64 dims of one head)
-    for (int i = tid; i < H * kLtDH; i += 256) {
+    for (int i = all; i < H * kLtDH; i += 256 * G) {
       const int hh = i >> 7, d = i & 127;
       const float qd = bf16_to_f32(qb[hh * (kLtDH + kLtDR) + d]);
       const float pw = wave_sum(qd * bf16_to_f32(ln_w[hh * kLtHeadW + d]));
@@ -165,12 +183,13 @@ __global__ __launch_bounds__(256, 2) void literal_tile_kernel(
       }
     }
     __syncthreads();
-    for (int hh = tid; hh < H; hh += 256) {
+    for (int hh = all; hh < H; hh += 256 * G) {
       sqw[hh] = kd[4 * hh] + kd[4 * hh + 2];
       sqb[hh] = kd[4 * hh + 1] + kd[4 * hh + 3];
     }
   }
-  // moments of the token's x - K (K: the pivot) and the key dots sum q w (x - K)
+  // moments of the token's x - K over the group's heads (K: the group's pivot)
+  // and the key dots sum q w (x - K)
   float s1 = 0.f, s2 = 0.f, K = 0.f;
   auto block = [&](int head, int blk, float& kdp) {
     lt_f32x16_t acc;
@@ -181,23 +200,24 @@ __global__ __launch_bounds__(256, 2) void literal_tile_kernel(
     for (int c = 0; c < kLtDC / 16; ++c)
       acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*reinterpret_cast<const bf16x8_t*>(arow + 16 * c), cb[c], acc, 0,
                                                     0, 0);
-    // lane holds outputs 32 blk + 8 qq + 4 hf + e of its token in acc[4 qq + e]
+    // lane holds outputs 32 blk + 16 hf + 4 qq + e of its token in acc[4 qq + e]
     if (LN && blk == 0) {
-      // pivot: the token's first gated value (output 0 of head 0, in the lane
-      // half hf = 0), the same in both halves; set on the first head only
+      // pivot: the token's first gated value (output 0 of the group's first
+      // head, in the lane half hf = 0), the same in both halves; set on the
+      // first head only
       const uint32_t gw = gv[0][0][0];
       const float x0 = ADD ? acc[0] + bf16_lo(gw) : acc[0] * bf16_lo(gw);
       const uint32_t u = __float_as_uint(x0);
       const auto sw = __builtin_amdgcn_permlane32_swap(u, u, false, false);
-      K = head == 0 ? __uint_as_float(sw[0]) : K;
+      K = head == h0 ? __uint_as_float(sw[0]) : K;
     }
 #pragma unroll
     for (int qq = 0; qq < 4; ++qq) {
       float4 qa = make_float4(0.f, 0.f, 0.f, 0.f);
-      if (blk < 4) qa = *reinterpret_cast<const float4*>(ob + 32 * blk + 8 * qq + 4 * hf);
+      if (blk < 4) qa = *reinterpret_cast<const float4*>(ob + 32 * blk + 16 * hf + 4 * qq);
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        const uint32_t gw = gv[blk & 3][qq][e >> 1];
+        const uint32_t gw = gv[blk & 3][qq >> 1][2 * (qq & 1) + (e >> 1)];
         const float g = (e & 1) ? bf16_hi(gw) : bf16_lo(gw);
         const float x = (ADD ? acc[4 * qq + e] + g : acc[4 * qq + e] * g) - K;  // K = 0 without a LayerNorm
         if (LN) {
@@ -207,16 +227,16 @@ __global__ __launch_bounds__(256, 2) void literal_tile_kernel(
         if (blk < 4) kdp = fmaf((&qa.x)[e], x, kdp);
       }
     }
-    const int nxt = min(head + 1, H - 1);
+    const int nxt = min(head + 1, h0 + Hn - 1);
     if (blk + 4 < NB)
       fetch_g(head, blk + 4);
     else
       fetch_g(nxt, blk + 4 - NB);
     __builtin_amdgcn_sched_barrier(0);  // one block's operands and accumulator live at a time
   };
-  for (int head = 0; head < H; ++head) {
+  for (int head = h0; head < h0 + Hn; ++head) {
     // the next head's operands (the last head fetches itself again: no branch in the loop)
-    const int nxt = min(head + 1, H - 1);
+    const int nxt = min(head + 1, h0 + Hn - 1);
     __syncthreads();  // K half and q w of this head visible; the V half is free
     if (LN) put_half(1);
     fetch_half(w_uk, nxt);
@@ -255,31 +275,48 @@ __global__ __launch_bounds__(256, 2) void literal_tile_kernel(
 #pragma unroll
     for (int k = 0; k < 8; ++k) g[k] = ld_lane16(gate + head * kLtHeadW + kLtDH, goff[k]);
   };
-  fetch_v(0);
-  fetch_gt(ga, 0);
-  fetch_gt(gb, min(1, H - 1));
+  fetch_v(h0);
+  fetch_gt(ga, h0);
+  fetch_gt(gb, h0 + min(1, Hn - 1));
   u32x4_t kr[2];  // q^R . k^R: lane half hf takes RoPE dims 32 hf .. + 31
   kr[0] = *reinterpret_cast<const u32x4_t*>(cache + row * (kLtDC + kLtDR) + kLtDC + 32 * hf);
   kr[1] = *reinterpret_cast<const u32x4_t*>(cache + row * (kLtDC + kLtDR) + kLtDC + 32 * hf + 8);
   u32x4_t kr2[2];
   kr2[0] = *reinterpret_cast<const u32x4_t*>(cache + row * (kLtDC + kLtDR) + kLtDC + 32 * hf + 16);
   kr2[1] = *reinterpret_cast<const u32x4_t*>(cache + row * (kLtDC + kLtDR) + kLtDC + 32 * hf + 24);
+  // the group's moments of each token, about its own pivot
+  const float m1 = LN ? lane_half_sum(s1) / static_cast<float>(Hn * kLtHeadW) : 0.f;
+  const float m2 = LN ? lane_half_sum(s2) / static_cast<float>(Hn * kLtHeadW) : 0.f;
+  if (LN && G > 1 && hf == 0) {
+    float* mp = mst + grp * 3 * 128 + w * 32 + t;
+    mp[0] = K;
+    mp[128] = m1;
+    mp[256] = fmaxf(m2 - m1 * m1, 0.f);
+  }
   __syncthreads();  // region R is free
   float* qrs = reinterpret_cast<float*>(lt_lds);  // [H][d_r]
-  for (int i = tid; i < H * kLtDR; i += 256) qrs[i] = bf16_to_f32(qb[(i >> 6) * (kLtDH + kLtDR) + kLtDH + (i & 63)]);
+  for (int i = all; i < H * kLtDR; i += 256 * G) qrs[i] = bf16_to_f32(qb[(i >> 6) * (kLtDH + kLtDR) + kLtDH + (i & 63)]);
   float mu = 0.f, dmu = 0.f, rstd = 1.f;  // mean, mean - K, 1 / sigma
   if (LN) {
     // moments about the pivot: m1 = mean(x - K) is of the size of sigma or a
     // few sigma, so m2 - m1^2 keeps its precision
-    const float m1 = lane_half_sum(s1) / static_cast<float>(width);
-    const float m2 = lane_half_sum(s2) / static_cast<float>(width);
+    float var = fmaxf(m2 - m1 * m1, 0.f);
     dmu = m1;
-    mu = K + m1;
-    rstd = 1.0f / sqrtf(fmaxf(m2 - m1 * m1, 0.f) + kLtLnEps);
-    if (hf == 0) mus[w * 32 + t] = mu;
+    if (G > 1) {
+      // the other group's half of the dims: with d the difference of the two
+      // means, the token's mean is half of d away from each, and the variance
+      // the mean of the two plus d^2 / 4
+      const float* mp = mst + (1 - grp) * 3 * 128 + w * 32 + t;
+      const float d = (mp[0] - K) + (mp[128] - m1);
+      dmu = fmaf(0.5f, d, m1);
+      var = fmaf(0.25f * d, d, 0.5f * (var + mp[256]));
+    }
+    mu = K + dmu;
+    rstd = 1.0f / sqrtf(var + kLtLnEps);
+    if (grp == 0 && hf == 0) mus[w * 32 + t] = mu;
   }
   __syncthreads();
-  for (int head = 0; head < H; ++head) {
+  for (int head = h0; head < h0 + Hn; ++head) {
     const float* qr = qrs + head * kLtDR + 32 * hf;
     float rp = 0.f;
 #pragma unroll
@@ -301,7 +338,7 @@ __global__ __launch_bounds__(256, 2) void literal_tile_kernel(
     if (lane == 0) wr[w * H + head] = wm;
   }
   __syncthreads();
-  for (int head = 0; head < H; ++head) {
+  for (int head = h0; head < h0 + Hn; ++head) {
     const float m = fmaxf(fmaxf(wr[head], wr[H + head]), fmaxf(wr[2 * H + head], wr[3 * H + head]));
     float* kp = kd + (w * H + head) * 32 + t;
     const float p = exp2f(*kp - m);  // 0 past the sequence
@@ -313,7 +350,7 @@ __global__ __launch_bounds__(256, 2) void literal_tile_kernel(
     if (lane == 0) wr[(4 + w) * H + head] = sp;
   }
   __syncthreads();
-  for (int hh = tid; hh < H; hh += 256) {
+  for (int hh = all; hh < H; hh += 256 * G) {
     float* rec = pb + hh * (kLtDV + 4) + kLtDV;
     rec[0] = fmaxf(fmaxf(wr[hh], wr[H + hh]), fmaxf(wr[2 * H + hh], wr[3 * H + hh]));
     rec[1] = (wr[4 * H + hh] + wr[5 * H + hh]) + (wr[6 * H + hh] + wr[7 * H + hh]);
@@ -381,32 +418,33 @@ __global__ __launch_bounds__(256, 2) void literal_tile_kernel(
   // set is refilled two heads ahead, the W_UV rows one head ahead
   // (whole pairs in the loop and an odd last head after it, so the loop's back
   // edge follows the odd head and the waits at its top stay partial)
-  int head = 0;
-  for (; head + 1 < H; head += 2) {
+  int head = h0;
+  const int he = h0 + Hn;
+  for (; head + 1 < he; head += 2) {
     __syncthreads();  // R and ob are free (previous head computed, its sums read)
-    if (head > 0) flush(head - 1);
+    if (head > h0) flush(head - 1);
     stage(ga);
     __syncthreads();
     fetch_v(head + 1);
-    fetch_gt(ga, min(head + 2, H - 1));
+    fetch_gt(ga, min(head + 2, he - 1));
     values(head);
     __syncthreads();
     flush(head);
     stage(gb);
     __syncthreads();
-    fetch_v(min(head + 2, H - 1));
-    fetch_gt(gb, min(head + 3, H - 1));
+    fetch_v(min(head + 2, he - 1));
+    fetch_gt(gb, min(head + 3, he - 1));
     values(head + 1);
   }
-  if (head < H) {  // the last of an odd head count: its operands are in vs and ga
+  if (head < he) {  // the last of an odd head count: its operands are in vs and ga
     __syncthreads();
-    if (head > 0) flush(head - 1);
+    if (head > h0) flush(head - 1);
     stage(ga);
     __syncthreads();
     values(head);
   }
   __syncthreads();
-  flush(H - 1);
+  flush(he - 1);
 }
 
 // out[b, h, v] from the tiles' partials: rescale to the common max, then the
@@ -779,13 +817,19 @@ extern "C" eg_mla_status eg_mla_decode_literal(const eg_mla_dims* dims, int32_t 
                        cap, tiles, H, d.head_dim, d.v_head_dim, out);
     return hipGetLastError() == hipSuccess ? EG_MLA_OK : EG_MLA_ERR_HIP;
   }
-  const auto kern = use_ln ? (add ? literal_tile_kernel<true, true> : literal_tile_kernel<true, false>)
-                           : (add ? literal_tile_kernel<false, true> : literal_tile_kernel<false, false>);
-  const int lds = static_cast<int>(literal_lds_bytes(H));
+  const int groups = literal_head_groups(H);
+  auto pick_tile = [&](auto g) {
+    constexpr int G = decltype(g)::value;
+    return use_ln ? (add ? literal_tile_kernel<true, true, G> : literal_tile_kernel<true, false, G>)
+                  : (add ? literal_tile_kernel<false, true, G> : literal_tile_kernel<false, false, G>);
+  };
+  const auto kern =
+      groups == 2 ? pick_tile(std::integral_constant<int, 2>{}) : pick_tile(std::integral_constant<int, 1>{});
+  const int lds = static_cast<int>(literal_lds_bytes(H, groups));
   if (hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, lds) !=
       hipSuccess)
     return EG_MLA_ERR_HIP;
-  hipLaunchKernelGGL(kern, dim3(tiles, batch), dim3(256), lds, stream, static_cast<const uint16_t*>(q),
+  hipLaunchKernelGGL(kern, dim3(tiles, batch), dim3(256 * groups), lds, stream, static_cast<const uint16_t*>(q),
                      static_cast<const uint16_t*>(latent_cache), token_id_cache, static_cast<const uint16_t*>(gate_full),
                      static_cast<const uint16_t*>(w_uk), static_cast<const uint16_t*>(w_uv),
                      static_cast<const uint16_t*>(ln_weight), static_cast<const uint16_t*>(ln_bias), seq_lens,

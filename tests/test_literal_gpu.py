@@ -95,6 +95,37 @@ def test_literal_layernorm_offset_rows(gpu):
                  "literal add, offset rows")
 
 
+@pytest.mark.parametrize("heads,flags,mode,use_ln", [
+    (2, 0, "mul", True),                                    # one head per group
+    (6, B.LITERAL_ADD, "add", True),                        # three per group: a pair, then the last alone
+    (28, 0, "mul", True),                                   # the most heads two weight regions leave LDS for
+    (30, B.LITERAL_NO_LN, "mul", False),                    # one group again
+], ids=["h2", "h6", "h28", "h30"])
+def test_literal_head_groups(gpu, heads, flags, mode, use_ln):
+    wl = W.WORKLOADS[1].replace(batch=2, heads=heads, seq_len=None, seq_len_range=(1, 161), vocab=600, seed=88)
+    inp = W.generate(wl, seq_lens=np.array([161, 33]))
+    lg = W.generate_literal_gate(wl)
+    say(f"literal decode head groups H={heads} mode={mode}")
+    assert_close(run_literal(inp, lg, flags), oracle_literal(inp, lg, mode, use_ln), "bf16",
+                 f"literal head groups H={heads}")
+
+
+def test_literal_layernorm_groups_apart(gpu):
+    # the two halves of the heads centred at 96 and -32 (each about 100 times
+    # its spread): the moments of the halves, about pivots far apart, combine
+    # to the oracle's two-pass moments
+    wl = W.WORKLOADS[1].replace(batch=2, seq_len=None, seq_len_range=(1, 200), vocab=400, seed=89)
+    inp = W.generate(wl, seq_lens=np.array([200, 17]))
+    lg = W.generate_literal_gate(wl, center=96.0)
+    half = lg.gate_full.shape[1] // 2
+    gate = W.bf16_bits_to_f32(lg.gate_full)
+    gate[:, half:] -= np.float32(128.0)
+    lg.gate_full = W.f32_to_bf16_bits(gate)
+    say("literal decode additive gate, head groups centred apart")
+    assert_close(run_literal(inp, lg, B.LITERAL_ADD), oracle_literal(inp, lg, "add", True), "bf16",
+                 "literal add, groups apart")
+
+
 def test_literal_full_size_sampled(gpu):
     # the bench's workload and launch (B32 H16 L4096, 50304 gate rows, LayerNorm);
     # the oracle recomputes two sampled sequences on their own, from their cache
