@@ -197,7 +197,7 @@ extern "C" eg_mla_status eg_mla_prefill_varlen(const eg_mla_dims* dims, int32_t 
                        stream, x);
     return hipGetLastError() == hipSuccess ? EG_MLA_OK : EG_MLA_ERR_HIP;
   }
-  // q_lat (bf16) and q^R for every token
+  // q_lat (fp16) of every token
   const int side_wgs = ((T + kPfUvTokens - 1) / kPfUvTokens + kPfSideChunks - 1) / kPfSideChunks;
   hipLaunchKernelGGL(prefill_absorb_kernel, dim3(side_wgs, d.num_heads), dim3(256), 0, stream,
                      static_cast<const uint16_t*>(q), static_cast<const uint16_t*>(w_uk), qf, T);
@@ -208,6 +208,7 @@ extern "C" eg_mla_status eg_mla_prefill_varlen(const eg_mla_dims* dims, int32_t 
                      token_ids, static_cast<const uint16_t*>(gate_table), ct, T, d.vocab_size);
   PrefillArgs a;
   a.qf = qf;
+  a.q = static_cast<const uint16_t*>(q);
   a.latent = static_cast<const uint16_t*>(latent);
   a.ct = ct;
   a.seq_start = seq_start;

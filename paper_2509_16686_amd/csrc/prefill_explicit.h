@@ -110,11 +110,12 @@ __global__ __launch_bounds__(256, 2) void prefill_x_proj_kernel(const uint16_t* 
     const int kb = kPxRowB * step;  // byte offset of the step's 32 k in a row
     // wave w (uniform) takes one region: 0 hi rows, 1 lo rows, 2 W_UK rows, 3 W_UV rows
     const __amdgpu_buffer_rsrc_t rs = w == 0 ? rh : w == 1 ? rl : w == 2 ? rk : rv;
-    const int nrow = w < 2 ? ntok : kPxDH;  // rows of the region (latent rows past the end repeat the last)
+    const int nrow = ntok;  // latent rows past the end repeat the last
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
       const int I = 8 * w + j, row = 16 * I + (lane >> 2), piece = (lane & 3) ^ px_swz(row);
-      const int r = min(row & (kPxTok - 1), nrow - 1);  // row within the region
+      // row within the region; weight rows in pf_out_row order
+      const int r = w < 2 ? min(row & (kPxTok - 1), nrow - 1) : pf_out_row(row & (kPxTok - 1));
       __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, lds_ptr(base + 16 * I * kPxRowB), 16, r * DC * 2 + kb + 16 * piece,
                                                0, 0, 0);
     }
@@ -173,20 +174,22 @@ __global__ __launch_bounds__(256, 2) void prefill_x_proj_kernel(const uint16_t* 
     step_landed();
     __syncthreads();
   }
-  // lane holds dims 32 ob + 8 q + 4 h + (0..3) of token 64 wt + 32 tb + r32 in acc[tb][ob][4 q + (0..3)]
+  // lane holds dims 32 ob + 16 i + 8 h + (0..7) of token 64 wt + 32 tb + r32 in acc[tb][ob][8 i + (0..7)]
   uint16_t* dst = wo == 0 ? kc : vv;
 #pragma unroll
   for (int tb = 0; tb < 2; ++tb) {
     const int t = t0 + 64 * wt + 32 * tb + r32;
     if (t >= T) break;
-    uint16_t* row = dst + (static_cast<int64_t>(hh) * T + t) * kPxDH + 4 * h;
+    uint16_t* row = dst + (static_cast<int64_t>(hh) * T + t) * kPxDH + 8 * h;
 #pragma unroll
     for (int ob = 0; ob < 4; ++ob)
 #pragma unroll
-      for (int q = 0; q < 4; ++q)
-        *reinterpret_cast<u32x2_t*>(row + 32 * ob + 8 * q) =
-            u32x2_t{pack_f16x2(acc[tb][ob][4 * q], acc[tb][ob][4 * q + 1]),
-                    pack_f16x2(acc[tb][ob][4 * q + 2], acc[tb][ob][4 * q + 3])};
+      for (int i = 0; i < 2; ++i)
+        *reinterpret_cast<u32x4_t*>(row + 32 * ob + 16 * i) =
+            u32x4_t{pack_f16x2(acc[tb][ob][8 * i], acc[tb][ob][8 * i + 1]),
+                    pack_f16x2(acc[tb][ob][8 * i + 2], acc[tb][ob][8 * i + 3]),
+                    pack_f16x2(acc[tb][ob][8 * i + 4], acc[tb][ob][8 * i + 5]),
+                    pack_f16x2(acc[tb][ob][8 * i + 6], acc[tb][ob][8 * i + 7])};
   }
 }
 
@@ -317,9 +320,11 @@ __global__ __launch_bounds__(256, 2) void prefill_x_attn_kernel(PrefillXArgs a) 
   const int swz_sk = pf_lat_swz(r32);
   const int off_sr = kPxRopeOff + r32 * kPxRopeRow;
   const int swz_sr = pf_rope_swz(r32);
-  // value A (transposed reads): rows 16 m + 4 h + r16 / 4 (+ 8), byte 8 (r16 % 2) of the piece
-  const int off_v = kPxVOff + (4 * h + (r16 >> 2)) * kPxKcRow + 8 * (r16 & 1);
-  const int vlo = 2 * R1 + ((r16 & 3) >> 1);  // low 2 bits of the logical piece
+  // value A (transposed reads): rows 16 m + 4 h + r16 / 4 (+ 8); operand row 16 R1 + 4 j + e takes
+  // dim 16 R1 + 8 (j % 2) + 4 (j / 2) + e (pf_out_row), so lane r16 (j = r16 % 4) addresses
+  // byte 8 (j / 2) of the piece
+  const int off_v = kPxVOff + (4 * h + (r16 >> 2)) * kPxKcRow + 8 * ((r16 & 3) >> 1);
+  const int vlo = 2 * R1 + (r16 & 1);  // low 2 bits of the logical piece
 
   pf_f32x16_t o[kPxDH / 32];
 #pragma unroll
@@ -441,17 +446,19 @@ __global__ __launch_bounds__(256, 2) void prefill_x_attn_kernel(PrefillXArgs a) 
     if (i + 1 < ntiles) step(i + 1, lds1, lds0);
   }
 
-  // ---- out = O / l in bf16: lane holds dims 32 db + 8 q + 4 h + 0..3 of its row ----
+  // ---- out = O / l in bf16: lane holds dims 32 db + 16 i + 8 h + 0..7 of its row in o[db][8 i + 0..7] ----
   const float inv = 1.0f / pf_pair_sum(l_run);
   if (row_ok) {
-    uint16_t* orow = a.out + (static_cast<int64_t>(t_row) * a.H + hh) * kPxDH + 4 * h;
+    uint16_t* orow = a.out + (static_cast<int64_t>(t_row) * a.H + hh) * kPxDH + 8 * h;
 #pragma unroll
     for (int db = 0; db < kPxDH / 32; ++db)
 #pragma unroll
-      for (int q = 0; q < 4; ++q)
-        *reinterpret_cast<u32x2_t*>(orow + 32 * db + 8 * q) =
-            u32x2_t{pack_bf16x2(o[db][4 * q] * inv, o[db][4 * q + 1] * inv),
-                    pack_bf16x2(o[db][4 * q + 2] * inv, o[db][4 * q + 3] * inv)};
+      for (int i = 0; i < 2; ++i)
+        *reinterpret_cast<u32x4_t*>(orow + 32 * db + 16 * i) =
+            u32x4_t{pack_bf16x2(o[db][8 * i] * inv, o[db][8 * i + 1] * inv),
+                    pack_bf16x2(o[db][8 * i + 2] * inv, o[db][8 * i + 3] * inv),
+                    pack_bf16x2(o[db][8 * i + 4] * inv, o[db][8 * i + 5] * inv),
+                    pack_bf16x2(o[db][8 * i + 6] * inv, o[db][8 * i + 7] * inv)};
   }
 }
 

@@ -14,7 +14,7 @@
 //
 // Five launches: a map from each token to its sequence's first token; the
 // gated latent of every token (fp16, once: the attention's keys and values);
-// the absorption (q_lat in fp16, q^R copied in bf16, for every token); the
+// the absorption (q_lat in fp16, for every token); the
 // attention kernel below, which writes o_lat / l in fp16; and the
 // up-projection by W_UV per head (W_UV converted exactly to fp16).
 //
@@ -83,6 +83,14 @@ typedef __attribute__((ext_vector_type(16))) float pf_f32x16_t;
 
 __device__ __forceinline__ int pf_lat_swz(int key) { return ((key & 3) << 2) | ((key >> 2) & 3); }
 __device__ __forceinline__ int pf_rope_swz(int key) { return (key >> 1) & 7; }
+// Operand row that holds output i (swaps bits 2 and 3; its own inverse).  A
+// 32x32 accumulator lane of half h holds rows 8 q + 4 h + e, which are then the
+// outputs 16 (q / 2) + 8 h + 4 (q % 2) + e: 8 adjacent ones per pair of q, and
+// the two halves' 16-byte stores meet.  With rows in output order each store
+// was 8 bytes, twice the requests: of 20384 tokens x 16 heads the absorption
+// took 82 us (with its copy of q^R, which the attention now reads itself) and
+// the up-projection 59.
+__device__ __forceinline__ int pf_out_row(int i) { return (i & ~12) | ((i & 4) << 1) | ((i & 8) >> 1); }
 
 // Maximum and sum of lanes i and i ^ 32, the same value (same order) in both.
 __device__ __forceinline__ float pf_pair_max(float x) {
@@ -129,7 +137,8 @@ __global__ __launch_bounds__(256) void prefill_gate_kernel(const uint16_t* __res
 constexpr int kPfBufRsrcWord3 = 0x00020000;
 
 struct PrefillArgs {
-  const uint16_t* qf;          // [T][16][192]: q_lat fp16 | q^R bf16
+  const uint16_t* qf;          // [T][16][128] fp16: q_lat
+  const uint16_t* q;           // [T][16][192] bf16: q^C | q^R
   const uint16_t* latent;      // [T][192] bf16: c | k^R
   const uint16_t* ct;          // [T][128] fp16: gated latent
   const int32_t* seq_start;    // [T]
@@ -161,11 +170,13 @@ __global__ __launch_bounds__(kPfThreads, 2) void prefill_attn_mfma_kernel(Prefil
   f16x8_t qv[kPfDC / 16];   // q_lat (fp16)
   bf16x8_t qr[kPfDR / 16];  // q^R (bf16)
   {
-    const uint16_t* qrow = a.qf + (static_cast<int64_t>(t_c) * kPfHeads + head) * kPfDQ + 8 * h;
+    const int64_t row = static_cast<int64_t>(t_c) * kPfHeads + head;
+    const uint16_t* qrow = a.qf + row * kPfDC + 8 * h;
+    const uint16_t* rrow = a.q + row * kPfDQ + kPfDC + 8 * h;
 #pragma unroll
     for (int c = 0; c < kPfDC / 16; ++c) qv[c] = *reinterpret_cast<const f16x8_t*>(qrow + 16 * c);
 #pragma unroll
-    for (int c = 0; c < kPfDR / 16; ++c) qr[c] = *reinterpret_cast<const bf16x8_t*>(qrow + kPfDC + 16 * c);
+    for (int c = 0; c < kPfDR / 16; ++c) qr[c] = *reinterpret_cast<const bf16x8_t*>(rrow + 16 * c);
   }
 
   // tile copies into LDS: wave w issues latent instructions I = 4 w + j (keys
@@ -203,9 +214,11 @@ __global__ __launch_bounds__(kPfThreads, 2) void prefill_attn_mfma_kernel(Prefil
   const int swz_sl = pf_lat_swz(r32);
   const int off_sr = kPfRopeOff + r32 * kPfRopeRow;
   const int swz_sr = pf_rope_swz(r32);
-  // value A (transposed reads): rows 16 m + 4 h + r16 / 4 (+ 8), byte 8 (r16 % 2) of the piece
-  const int off_v = (4 * h + (r16 >> 2)) * kPfLatRow + 8 * (r16 & 1);
-  const int vlo = 2 * R1 + ((r16 & 3) >> 1);  // low 2 bits of the logical piece
+  // value A (transposed reads): rows 16 m + 4 h + r16 / 4 (+ 8); operand row 16 R1 + 4 j + e takes
+  // dim 16 R1 + 8 (j % 2) + 4 (j / 2) + e (pf_out_row), so lane r16 (j = r16 % 4) addresses
+  // byte 8 (j / 2) of the piece
+  const int off_v = (4 * h + (r16 >> 2)) * kPfLatRow + 8 * ((r16 & 3) >> 1);
+  const int vlo = 2 * R1 + (r16 & 1);  // low 2 bits of the logical piece
 
   pf_f32x16_t o[kPfDC / 32];
 #pragma unroll
@@ -327,28 +340,30 @@ __global__ __launch_bounds__(kPfThreads, 2) void prefill_attn_mfma_kernel(Prefil
     if (i + 1 < ntiles) step(i + 1, lds1, lds0);
   }
 
-  // ---- o_lat / l: lane holds dims 32 db + 8 q + 4 h + 0..3 of its row ----
+  // ---- o_lat / l: lane holds dims 32 db + 16 i + 8 h + 0..7 of its row in o[db][8 i + 0..7] ----
   const float inv = 1.0f / pf_pair_sum(l_run);
   if (row_ok) {
-    uint16_t* orow = a.olat + (static_cast<int64_t>(t_row) * kPfHeads + head) * kPfDC + 4 * h;
+    uint16_t* orow = a.olat + (static_cast<int64_t>(t_row) * kPfHeads + head) * kPfDC + 8 * h;
 #pragma unroll
     for (int db = 0; db < kPfDC / 32; ++db)
 #pragma unroll
-      for (int q = 0; q < 4; ++q)
-        *reinterpret_cast<u32x2_t*>(orow + 32 * db + 8 * q) =
-            u32x2_t{pack_f16x2(o[db][4 * q] * inv, o[db][4 * q + 1] * inv),
-                    pack_f16x2(o[db][4 * q + 2] * inv, o[db][4 * q + 3] * inv)};
+      for (int i = 0; i < 2; ++i)
+        *reinterpret_cast<u32x4_t*>(orow + 32 * db + 16 * i) =
+            u32x4_t{pack_f16x2(o[db][8 * i] * inv, o[db][8 * i + 1] * inv),
+                    pack_f16x2(o[db][8 * i + 2] * inv, o[db][8 * i + 3] * inv),
+                    pack_f16x2(o[db][8 * i + 4] * inv, o[db][8 * i + 5] * inv),
+                    pack_f16x2(o[db][8 * i + 6] * inv, o[db][8 * i + 7] * inv)};
   }
 }
 
-// q_lat[t, h, :] = W_UK[h]^T q^C[t, h, :] in fp16, and q^R copied in bf16, for up to
-// 4 chunks of 128 tokens of one head per work-group (4 waves of 32 tokens; the
-// next chunk's rows load while a chunk computes and stores).  W_UK[h]
-// ([d_h][d_c] row-major, rows padded to 288 bytes) is staged in LDS once and
-// read back as the A operand of v_mfma_f32_32x32x16_bf16 with
+// q_lat[t, h, :] = W_UK[h]^T q^C[t, h, :] in fp16, for up to 4 chunks of 128
+// tokens of one head per work-group (4 waves of 32 tokens; the next chunk's
+// rows load while a chunk computes and stores).  W_UK[h] ([d_h][d_c]
+// row-major, rows padded to 288 bytes, columns in pf_out_row order) is staged
+// in LDS once and read back as the A operand of v_mfma_f32_32x32x16_bf16 with
 // ds_read_b64_tr_b16 (one output column per lane, 4 consecutive rows per
 // read); the query rows come straight from global as the B operand, and the
-// accumulator holds q_lat^T, stored 4 consecutive columns at a time.
+// accumulator holds q_lat^T, stored 8 consecutive columns at a time.
 __global__ __launch_bounds__(256) void prefill_absorb_kernel(const uint16_t* __restrict__ q,
                                                              const uint16_t* __restrict__ w_uk,
                                                              uint16_t* __restrict__ qf, int T) {
@@ -359,27 +374,21 @@ __global__ __launch_bounds__(256) void prefill_absorb_kernel(const uint16_t* __r
   const int nch = min(kPfSideChunks, (T + kPfUvTokens - 1) / kPfUvTokens - c0);
   const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, r32 = lane & 31, h = lane >> 5;
   const int r16 = lane & 15, R1 = (lane >> 4) & 1;
-  // a chunk's operands: the lane's token's q^C (B operand) and, per thread, 32
-  // dims (4 x 16 bytes) of q^R of token t0 + tid / 2 (copied through)
+  // a chunk's operand: the lane's token's q^C (B operand)
   bf16x8_t qb[DH / 16];
-  u32x4_t rq[4];
   auto load = [&](int chunk) {
     const int t0 = chunk * kPfUvTokens;
     const int tc = min(t0 + 32 * w + r32, T - 1);
     const uint16_t* qrow = q + (static_cast<int64_t>(tc) * kPfHeads + hh) * DQin + 8 * h;
 #pragma unroll
     for (int c = 0; c < DH / 16; ++c) qb[c] = *reinterpret_cast<const bf16x8_t*>(qrow + 16 * c);
-    const int rt = min(t0 + (tid >> 1), T - 1);
-#pragma unroll
-    for (int j = 0; j < 4; ++j)
-      rq[j] = *reinterpret_cast<const u32x4_t*>(q + (static_cast<int64_t>(rt) * kPfHeads + hh) * DQin + DH +
-                                                32 * (tid & 1) + 8 * j);
   };
   load(c0);
   for (int p = tid; p < DH * kPfDC / 8; p += 256) {
     const int k = p / (kPfDC / 8), c8 = (p % (kPfDC / 8)) * 8;
-    *reinterpret_cast<u32x4_t*>(wk + k * RS + c8) =
-        *reinterpret_cast<const u32x4_t*>(w_uk + (static_cast<int64_t>(hh) * DH + k) * kPfDC + c8);
+    const u32x4_t v = *reinterpret_cast<const u32x4_t*>(w_uk + (static_cast<int64_t>(hh) * DH + k) * kPfDC + c8);
+    *reinterpret_cast<u32x2_t*>(wk + k * RS + pf_out_row(c8)) = u32x2_t{v[0], v[1]};
+    *reinterpret_cast<u32x2_t*>(wk + k * RS + pf_out_row(c8 + 4)) = u32x2_t{v[2], v[3]};
   }
   __syncthreads();
   // A operand of chunk c, column block cb: lane (column 32 cb + 16 R1 + r16) gets
@@ -405,27 +414,20 @@ __global__ __launch_bounds__(256) void prefill_absorb_kernel(const uint16_t* __r
         const bf16x8_t av = __builtin_bit_cast(bf16x8_t, __builtin_shufflevector(a0, a1, 0, 1, 2, 3, 4, 5, 6, 7));
         acc[cb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av, qb[c], acc[cb], 0, 0, 0);
       }
-    const u32x4_t r0 = rq[0], r1 = rq[1], r2 = rq[2], r3 = rq[3];
     // the next chunk's rows travel while this one is stored (the last chunk loads itself again)
     __builtin_amdgcn_sched_barrier(0);
     load(c0 + min(k + 1, nch - 1));
     __builtin_amdgcn_sched_barrier(0);
     if (t < T) {
-      uint16_t* dst = qf + (static_cast<int64_t>(t) * kPfHeads + hh) * kPfDQ + 4 * h;
+      uint16_t* dst = qf + (static_cast<int64_t>(t) * kPfHeads + hh) * kPfDC + 8 * h;
 #pragma unroll
       for (int cb = 0; cb < kPfDC / 32; ++cb)
 #pragma unroll
-        for (int qq = 0; qq < 4; ++qq)
-          *reinterpret_cast<u32x2_t*>(dst + 32 * cb + 8 * qq) =
-              u32x2_t{pack_f16x2(acc[cb][4 * qq], acc[cb][4 * qq + 1]),
-                      pack_f16x2(acc[cb][4 * qq + 2], acc[cb][4 * qq + 3])};
-    }
-    if (t0 + (tid >> 1) < T) {
-      uint16_t* dr = qf + (static_cast<int64_t>(t0 + (tid >> 1)) * kPfHeads + hh) * kPfDQ + kPfDC + 32 * (tid & 1);
-      *reinterpret_cast<u32x4_t*>(dr) = r0;
-      *reinterpret_cast<u32x4_t*>(dr + 8) = r1;
-      *reinterpret_cast<u32x4_t*>(dr + 16) = r2;
-      *reinterpret_cast<u32x4_t*>(dr + 24) = r3;
+        for (int i = 0; i < 2; ++i)
+          *reinterpret_cast<u32x4_t*>(dst + 32 * cb + 16 * i) =
+              u32x4_t{pack_f16x2(acc[cb][8 * i], acc[cb][8 * i + 1]), pack_f16x2(acc[cb][8 * i + 2], acc[cb][8 * i + 3]),
+                      pack_f16x2(acc[cb][8 * i + 4], acc[cb][8 * i + 5]),
+                      pack_f16x2(acc[cb][8 * i + 6], acc[cb][8 * i + 7])};
     }
   }
 }
@@ -436,8 +438,8 @@ __global__ __launch_bounds__(256) void prefill_absorb_kernel(const uint16_t* __r
 // converted to fp16 (exact for magnitudes between 2^-14 and 65504; smaller
 // weights become fp16 subnormals, an absolute error below 2^-25) in LDS as the
 // A operand, the fp16 o_lat rows straight from global as the B operand of
-// v_mfma_f32_32x32x16_f16; the accumulator holds out^T, stored 4 consecutive v
-// at a time.
+// v_mfma_f32_32x32x16_f16; the accumulator holds out^T (W_UV rows in
+// pf_out_row order), stored 8 consecutive v at a time.
 __global__ __launch_bounds__(256) void prefill_uv_kernel(const uint16_t* __restrict__ olat,
                                                          const uint16_t* __restrict__ w_uv,
                                                          uint16_t* __restrict__ out, int T) {
@@ -457,7 +459,7 @@ __global__ __launch_bounds__(256) void prefill_uv_kernel(const uint16_t* __restr
   load(c0);
   for (int p = tid; p < DV * kPfDC / 8; p += 256) {
     const int v = p / (kPfDC / 8), k8 = (p % (kPfDC / 8)) * 8;
-    *reinterpret_cast<u32x4_t*>(wl + v * RS + k8) =
+    *reinterpret_cast<u32x4_t*>(wl + pf_out_row(v) * RS + k8) =
         bf16x8_to_f16x8(*reinterpret_cast<const u32x4_t*>(w_uv + (static_cast<int64_t>(hh) * DV + v) * kPfDC + k8));
   }
   __syncthreads();
@@ -483,13 +485,14 @@ __global__ __launch_bounds__(256) void prefill_uv_kernel(const uint16_t* __restr
     load(c0 + min(k + 1, nch - 1));
     __builtin_amdgcn_sched_barrier(0);
     if (t < T) {
-      uint16_t* dst = out + (static_cast<int64_t>(t) * kPfHeads + hh) * DV + 4 * h;
+      uint16_t* dst = out + (static_cast<int64_t>(t) * kPfHeads + hh) * DV + 8 * h;
 #pragma unroll
       for (int vb = 0; vb < DV / 32; ++vb)
 #pragma unroll
-        for (int q = 0; q < 4; ++q)
-          *reinterpret_cast<u32x2_t*>(dst + 32 * vb + 8 * q) = u32x2_t{
-              pack_bf16x2(acc[vb][4 * q], acc[vb][4 * q + 1]), pack_bf16x2(acc[vb][4 * q + 2], acc[vb][4 * q + 3])};
+        for (int i = 0; i < 2; ++i)
+          *reinterpret_cast<u32x4_t*>(dst + 32 * vb + 16 * i) = u32x4_t{
+              pack_bf16x2(acc[vb][8 * i], acc[vb][8 * i + 1]), pack_bf16x2(acc[vb][8 * i + 2], acc[vb][8 * i + 3]),
+              pack_bf16x2(acc[vb][8 * i + 4], acc[vb][8 * i + 5]), pack_bf16x2(acc[vb][8 * i + 6], acc[vb][8 * i + 7])};
     }
   }
 }
