@@ -7,6 +7,7 @@
 // Deliberately simple: one work-group per (t, h), no tiling.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 
 #include "device_common.h"
@@ -165,9 +166,6 @@ extern "C" eg_mla_status eg_mla_prefill_varlen(const eg_mla_dims* dims, int32_t 
   int32_t* seq_start = reinterpret_cast<int32_t*>(ws + L.off_seq_start);
   uint16_t* qf = reinterpret_cast<uint16_t*>(ws + L.off_qf);
   uint16_t* olat = reinterpret_cast<uint16_t*>(ws + L.off_olat);
-
-  hipLaunchKernelGGL(prefill_seqmap_kernel, dim3((T + 255) / 256), dim3(256), 0, stream, cu_seqlens, batch, T,
-                     seq_start);
   if (!prefill_varlen_absorbed(d)) {
     // explicit form: K^C and V per head (fp16), then the attention per head
     uint16_t* kc = reinterpret_cast<uint16_t*>(ws + L.off_qf);
@@ -177,8 +175,8 @@ extern "C" eg_mla_status eg_mla_prefill_varlen(const eg_mla_dims* dims, int32_t 
     uint16_t* ct_lo = reinterpret_cast<uint16_t*>(ws + L.off_ct + align_up(static_cast<size_t>(T) * d.latent_dim * 2));
     const dim3 gate_grid(static_cast<unsigned>((static_cast<int64_t>(T) * (d.latent_dim / 8) + 255) / 256));
     hipLaunchKernelGGL(prefill_x_gate_kernel, gate_grid, dim3(256), 0, stream, static_cast<const uint16_t*>(latent),
-                       token_ids, static_cast<const uint16_t*>(gate_table), ct_hi, ct_lo, T, d.latent_dim,
-                       d.vocab_size);
+                       token_ids, static_cast<const uint16_t*>(gate_table), ct_hi, ct_lo, cu_seqlens, seq_start, T,
+                       d.latent_dim, d.vocab_size, batch);
     hipLaunchKernelGGL(prefill_x_proj_kernel, dim3((T + kPxTok - 1) / kPxTok, d.num_heads), dim3(256), 0, stream,
                        ct_hi, ct_lo, static_cast<const uint16_t*>(w_uk), static_cast<const uint16_t*>(w_uv), kc, vv, T,
                        d.latent_dim);
@@ -192,20 +190,31 @@ extern "C" eg_mla_status eg_mla_prefill_varlen(const eg_mla_dims* dims, int32_t 
     x.T = T;
     x.H = d.num_heads;
     x.DC = d.latent_dim;
+    x.head_group = px_head_group(d.num_heads);
     x.scale_log2 = softmax_scale(d) * 1.4426950408889634f;
     hipLaunchKernelGGL(prefill_x_attn_kernel, dim3(((T + kPxQTok - 1) / kPxQTok) * d.num_heads), dim3(256), 0,
                        stream, x);
     return hipGetLastError() == hipSuccess ? EG_MLA_OK : EG_MLA_ERR_HIP;
   }
-  // q_lat (fp16) of every token
-  const int side_wgs = ((T + kPfUvTokens - 1) / kPfUvTokens + kPfSideChunks - 1) / kPfSideChunks;
-  hipLaunchKernelGGL(prefill_absorb_kernel, dim3(side_wgs, d.num_heads), dim3(256), 0, stream,
-                     static_cast<const uint16_t*>(q), static_cast<const uint16_t*>(w_uk), qf, T);
-  // the gated latent of every token, once (keys and values of every head)
+  // q_lat (fp16) and the gated latent of every token (keys and values of every
+  // head).  A work-group of the side kernels takes as many chunks as leave two
+  // work-groups per compute unit, at most kPfSideChunks (the weights are then
+  // staged once for them): a chunk each below 8192 tokens.
+  const int nchunks = (T + kPfUvTokens - 1) / kPfUvTokens;
+  const int chunks = std::min(std::max(nchunks * kPfHeads / 512, 1), kPfSideChunks);
+  const int side_wgs = (nchunks + chunks - 1) / chunks;
   uint16_t* ct = reinterpret_cast<uint16_t*>(ws + L.off_ct);
-  const dim3 gate_grid(static_cast<unsigned>((static_cast<int64_t>(T) * 16 + 255) / 256));
-  hipLaunchKernelGGL(prefill_gate_kernel, gate_grid, dim3(256), 0, stream, static_cast<const uint16_t*>(latent),
-                     token_ids, static_cast<const uint16_t*>(gate_table), ct, T, d.vocab_size);
+  PfGateArgs ga;
+  ga.latent = static_cast<const uint16_t*>(latent);
+  ga.ids = token_ids;
+  ga.gate = static_cast<const uint16_t*>(gate_table);
+  ga.cu = cu_seqlens;
+  ga.ct = ct;
+  ga.seq_start = seq_start;
+  ga.V = d.vocab_size;
+  ga.B = batch;
+  hipLaunchKernelGGL(prefill_absorb_kernel, dim3(side_wgs, kPfHeads + kPfGateRows), dim3(256), 0, stream,
+                     static_cast<const uint16_t*>(q), static_cast<const uint16_t*>(w_uk), qf, T, chunks, ga);
   PrefillArgs a;
   a.qf = qf;
   a.q = static_cast<const uint16_t*>(q);
@@ -218,6 +227,6 @@ extern "C" eg_mla_status eg_mla_prefill_varlen(const eg_mla_dims* dims, int32_t 
   hipLaunchKernelGGL(prefill_attn_mfma_kernel, dim3((T + kPfTokens - 1) / kPfTokens), dim3(kPfThreads), 0, stream,
                      a);
   hipLaunchKernelGGL(prefill_uv_kernel, dim3(side_wgs, d.num_heads), dim3(256), 0, stream,
-                     olat, static_cast<const uint16_t*>(w_uv), static_cast<uint16_t*>(out), T);
+                     olat, static_cast<const uint16_t*>(w_uv), static_cast<uint16_t*>(out), T, chunks);
   return hipGetLastError() == hipSuccess ? EG_MLA_OK : EG_MLA_ERR_HIP;
 }

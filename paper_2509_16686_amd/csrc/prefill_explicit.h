@@ -9,8 +9,8 @@
 //   K^C[h][t] = W_UK[h] c~_t,  V[h][t] = W_UV[h] c~_t,  c~_t = c_t (.) G[id_t]
 //   out[t,h]  = sum_{j <= t, same sequence} softmax_j(tau (q^C[t,h].K^C[h][j] + q^R[t,h].k^R_j)) V[h][j]
 //
-// Two launches after the sequence map: the projection (a GEMM over d_c) and
-// the attention (a causal flash attention per head with 192-dim keys, the
+// Three launches: the gated latents with the map from each token to its
+// sequence's first token, the projection (a GEMM over d_c) and the attention (a causal flash attention per head with 192-dim keys, the
 // RoPE key shared by all heads, and 128-dim values).
 //
 // Precision.  The gated latent enters the projection as bf16 hi + lo (their
@@ -32,14 +32,20 @@ constexpr int kPxDH = 128, kPxDR = 64, kPxDK = kPxDH + kPxDR;  // key dims per h
 constexpr int kBufRsrcWord3 = 0x00020000;
 
 // ---------------------------------------------------------------------------
-// Gated latent, once per token: c~_t = c_t (.) G[id_t] as bf16 hi + lo rows
-// (ct_hi[t] + ct_lo[t] is the exact fp32 product), 8 dims per thread.
+// Gated latent, once per token: c~_t = c_t (.) G[id_t] as bf16 hi + lo (their
+// sum is the exact fp32 product), 8 dims per thread, in the order in which the
+// projection reads them: per block of 128 tokens (the last one shorter), per
+// step of 32 dims, the block's tokens (whole lines: 806 -> 799 us per call at
+// 4096 tokens of the 128-head layer).
 // ---------------------------------------------------------------------------
+constexpr int kPxTok = 128, kPxOut = 256, kPxK = 32;  // projection: tokens and outputs per work-group, dims per step
 __global__ __launch_bounds__(256) void prefill_x_gate_kernel(const uint16_t* __restrict__ latent,
                                                              const int32_t* __restrict__ ids,
                                                              const uint16_t* __restrict__ gate,
                                                              uint16_t* __restrict__ ct_hi, uint16_t* __restrict__ ct_lo,
-                                                             int T, int DC, int V) {
+                                                             const int32_t* __restrict__ cu,
+                                                             int32_t* __restrict__ seq_start, int T, int DC, int V,
+                                                             int B) {
   const int per = DC / 8;  // threads per token
   const int64_t i = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
   const int t = static_cast<int>(i / per), p = static_cast<int>(i % per);
@@ -48,8 +54,11 @@ __global__ __launch_bounds__(256) void prefill_x_gate_kernel(const uint16_t* __r
   const u32x4_t g = *reinterpret_cast<const u32x4_t*>(gate + static_cast<int64_t>(clamp_id(ids[t], V)) * DC + 8 * p);
   u32x4_t hi, lo;
   gate_chunk_hilo(c, g, hi, lo);
-  *reinterpret_cast<u32x4_t*>(ct_hi + static_cast<int64_t>(t) * DC + 8 * p) = hi;
-  *reinterpret_cast<u32x4_t*>(ct_lo + static_cast<int64_t>(t) * DC + 8 * p) = lo;
+  const int t0 = t / kPxTok * kPxTok, ntok = min(kPxTok, T - t0), step = p / (kPxK / 8);
+  const int64_t at = static_cast<int64_t>(t0) * DC + (step * ntok + t - t0) * kPxK + 8 * (p % (kPxK / 8));
+  *reinterpret_cast<u32x4_t*>(ct_hi + at) = hi;
+  *reinterpret_cast<u32x4_t*>(ct_lo + at) = lo;
+  if (p == 0) seq_start[t] = pf_seq_start(cu, B, t);
 }
 
 // ---------------------------------------------------------------------------
@@ -69,7 +78,6 @@ __global__ __launch_bounds__(256) void prefill_x_gate_kernel(const uint16_t* __r
 // (wo = 1): 2 x 4 tiles of v_mfma_f32_32x32x16_bf16, two products per tile
 // and step.
 // ---------------------------------------------------------------------------
-constexpr int kPxTok = 128, kPxOut = 256, kPxK = 32;
 constexpr int kPxRowB = 2 * kPxK;                          // bytes per staged row (64)
 constexpr int kPxRows = 2 * kPxTok + kPxOut;               // hi, lo, weights
 constexpr int kPxProjBuf = kPxRows * kPxRowB;              // bytes per buffer (32 KB)
@@ -107,7 +115,9 @@ __global__ __launch_bounds__(256, 2) void prefill_x_proj_kernel(const uint16_t* 
   // 16 I + lane / 4, slot lane % 4, which holds piece slot ^ swizzle(row)
   auto lds_ptr = [](unsigned char* p) { return (__attribute__((address_space(3))) void*)p; };
   auto issue_step = [&](int step, unsigned char* base) {
-    const int kb = kPxRowB * step;  // byte offset of the step's 32 k in a row
+    // byte offset of the step's 32 k: latent rows lie step by step, weight rows whole
+    const int kb = kPxRowB * step * (w < 2 ? ntok : 1);
+    const int stride = w < 2 ? kPxRowB : DC * 2;
     // wave w (uniform) takes one region: 0 hi rows, 1 lo rows, 2 W_UK rows, 3 W_UV rows
     const __amdgpu_buffer_rsrc_t rs = w == 0 ? rh : w == 1 ? rl : w == 2 ? rk : rv;
     const int nrow = ntok;  // latent rows past the end repeat the last
@@ -116,7 +126,7 @@ __global__ __launch_bounds__(256, 2) void prefill_x_proj_kernel(const uint16_t* 
       const int I = 8 * w + j, row = 16 * I + (lane >> 2), piece = (lane & 3) ^ px_swz(row);
       // row within the region; weight rows in pf_out_row order
       const int r = w < 2 ? min(row & (kPxTok - 1), nrow - 1) : pf_out_row(row & (kPxTok - 1));
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, lds_ptr(base + 16 * I * kPxRowB), 16, r * DC * 2 + kb + 16 * piece,
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, lds_ptr(base + 16 * I * kPxRowB), 16, r * stride + kb + 16 * piece,
                                                0, 0, 0);
     }
   };
@@ -238,8 +248,22 @@ struct PrefillXArgs {
   const int32_t* seq_start;    // [T]
   uint16_t* out;               // [T][H][128] bf16
   int T, H, DC;
+  int head_group;              // px_head_group(H)
   float scale_log2;            // tau log2(e)
 };
+
+// Heads whose blocks are launched together, heaviest first.  Head by head, an
+// XCD's last head starts its longest blocks when the others are almost done,
+// and the launch ends with them alone (128 heads, sequences of 1111 and 2985
+// tokens: 806 us per call against 768).  A group must not span two XCDs (one of
+// them would get its heaviest blocks), so it divides the H / 8 heads of an XCD;
+// beyond 8 heads the tail is short already and more heads only share the L2.
+inline int px_head_group(int H) {
+  if (H % 8 != 0) return 1;
+  int g = 8;
+  while ((H / 8) % g != 0) --g;
+  return g;
+}
 
 __global__ __launch_bounds__(256, 2) void prefill_x_attn_kernel(PrefillXArgs a) {
   // two tile buffers, distinct objects: the compiler then knows that a tile's
@@ -247,13 +271,14 @@ __global__ __launch_bounds__(256, 2) void prefill_x_attn_kernel(PrefillXArgs a) 
   // the copies before those reads
   __shared__ __attribute__((aligned(16))) unsigned char lds0[kPxTileBytes];
   __shared__ __attribute__((aligned(16))) unsigned char lds1[kPxTileBytes];
-  // one XCD takes whole heads (a contiguous range of the head-major order), so
+  // one XCD takes whole heads (a contiguous range of the group-major order), so
   // the blocks of a head read its K^C and V tiles through one L2 cache; within
-  // a head the last blocks of the stream (the heaviest) come first
+  // a group of heads the last blocks of the stream (the heaviest) come first
   const int nblk = (a.T + kPxQTok - 1) / kPxQTok;
   const int lb = xcd_logical_block(static_cast<int>(blockIdx.x), nblk * a.H);
-  const int hh = lb / nblk;
-  const int q0 = (nblk - 1 - lb % nblk) * kPxQTok;
+  const int in_group = lb % (nblk * a.head_group);
+  const int hh = lb / (nblk * a.head_group) * a.head_group + in_group % a.head_group;
+  const int q0 = (nblk - 1 - in_group / a.head_group) * kPxQTok;
   const int q_last = min(q0 + kPxQTok, a.T) - 1;
   const int kbeg = min(max(a.seq_start[q0], 0), q0);                 // keys from here ...
   const int kend = q_last + 1;                                       // ... to here (exclusive)

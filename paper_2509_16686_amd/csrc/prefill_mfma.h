@@ -12,11 +12,11 @@
 // the kernel is a multi-query flash attention with 192-dim keys and 128-dim
 // values.
 //
-// Five launches: a map from each token to its sequence's first token; the
-// gated latent of every token (fp16, once: the attention's keys and values);
-// the absorption (q_lat in fp16, for every token); the
-// attention kernel below, which writes o_lat / l in fp16; and the
-// up-projection by W_UV per head (W_UV converted exactly to fp16).
+// Three launches: the absorption (q_lat in fp16, for every token) with, in
+// work-groups of its own, the gated latent of every token (fp16, once: the
+// attention's keys and values) and the map from each token to its sequence's
+// first token; the attention kernel below, which writes o_lat / l in fp16; and
+// the up-projection by W_UV per head (W_UV converted exactly to fp16).
 //
 // Precision: the latent part of the attention runs on the fp16 MFMA.  q_lat
 // is one rounding of its fp32 sum to fp16, the gated latent one rounding of
@@ -77,7 +77,8 @@ constexpr int kPfRopeOff = kPfLatBytes;                           // after the l
 constexpr int kPfBufBytes = kPfRopeOff + kPfKeys * kPfRopeRow;    // one tile buffer (24 KB; two per work-group)
 static_assert(2 * 2 * kPfBufBytes <= 160 * 1024, "two work-groups of two tile buffers per compute unit");
 constexpr int kPfUvTokens = 128;  // absorption and up-projection: tokens per chunk (4 waves x 32)
-constexpr int kPfSideChunks = 4;  // chunks per work-group: the head's weights are staged once for them
+constexpr int kPfSideChunks = 4;  // chunks per work-group, at most: the head's weights are staged once for them
+constexpr int kPfGateRows = 16;   // rows of work-groups of the absorption launch that gate the latents
 
 typedef __attribute__((ext_vector_type(16))) float pf_f32x16_t;
 
@@ -104,32 +105,40 @@ __device__ __forceinline__ float pf_pair_sum(float x) {
   return __uint_as_float(s[0]) + __uint_as_float(s[1]);
 }
 
-// seq_start[t] = the first token of t's sequence (cu_seqlens[b] for the last b
-// with cu_seqlens[b] <= t), clamped into [0, t].
-__global__ __launch_bounds__(256) void prefill_seqmap_kernel(const int32_t* __restrict__ cu, int B, int T,
-                                                             int32_t* __restrict__ seq_start) {
-  const int t = blockIdx.x * 256 + threadIdx.x;
-  if (t >= T) return;
+// The first token of t's sequence (cu[b] for the last b with cu[b] <= t),
+// clamped into [0, t].
+__device__ __forceinline__ int pf_seq_start(const int32_t* __restrict__ cu, int B, int t) {
   int lo = 0, hi = B - 1;  // largest b in [0, B) with cu[b] <= t (b = 0 if none)
   while (lo < hi) {
     const int mid = (lo + hi + 1) >> 1;
     if (cu[mid] <= t) lo = mid;
     else hi = mid - 1;
   }
-  seq_start[t] = min(max(cu[lo], 0), t);
+  return min(max(cu[lo], 0), t);
 }
 
 // ct[t] = c_t (.) G[id_t] in fp16 (the exact fp32 products, each rounded
-// once): 16 threads per token, 8 dims each.
-__global__ __launch_bounds__(256) void prefill_gate_kernel(const uint16_t* __restrict__ latent,
-                                                           const int32_t* __restrict__ ids,
-                                                           const uint16_t* __restrict__ gate,
-                                                           uint16_t* __restrict__ ct, int T, int V) {
-  const int i = blockIdx.x * 256 + threadIdx.x, t = i >> 4, p = i & 15;
-  if (t >= T) return;
-  const u32x4_t c = *reinterpret_cast<const u32x4_t*>(latent + static_cast<int64_t>(t) * kPfDQ + 8 * p);
-  const u32x4_t g = *reinterpret_cast<const u32x4_t*>(gate + static_cast<int64_t>(clamp_id(ids[t], V)) * kPfDC + 8 * p);
-  *reinterpret_cast<u32x4_t*>(ct + static_cast<int64_t>(t) * kPfDC + 8 * p) = gate_chunk_f16(c, g);
+// once), 16 threads per token, 8 dims each; the first of them also writes
+// seq_start[t].  Work-group g of n.
+struct PfGateArgs {
+  const uint16_t* latent;
+  const int32_t* ids;
+  const uint16_t* gate;
+  const int32_t* cu;
+  uint16_t* ct;
+  int32_t* seq_start;
+  int V, B;
+};
+__device__ __forceinline__ void prefill_gate_part(const PfGateArgs& a, int T, int g, int n) {
+  for (int64_t i = static_cast<int64_t>(g) * 256 + threadIdx.x; i < static_cast<int64_t>(T) * 16;
+       i += static_cast<int64_t>(n) * 256) {
+    const int t = static_cast<int>(i >> 4), p = static_cast<int>(i & 15);
+    const u32x4_t c = *reinterpret_cast<const u32x4_t*>(a.latent + static_cast<int64_t>(t) * kPfDQ + 8 * p);
+    const u32x4_t w =
+        *reinterpret_cast<const u32x4_t*>(a.gate + static_cast<int64_t>(clamp_id(a.ids[t], a.V)) * kPfDC + 8 * p);
+    *reinterpret_cast<u32x4_t*>(a.ct + static_cast<int64_t>(t) * kPfDC + 8 * p) = gate_chunk_f16(c, w);
+    if (p == 0) a.seq_start[t] = pf_seq_start(a.cu, a.B, t);
+  }
 }
 
 // Word 3 of a raw buffer resource on gfx9 (32-bit data format; stride 0, so
@@ -356,22 +365,29 @@ __global__ __launch_bounds__(kPfThreads, 2) void prefill_attn_mfma_kernel(Prefil
   }
 }
 
-// q_lat[t, h, :] = W_UK[h]^T q^C[t, h, :] in fp16, for up to 4 chunks of 128
+// q_lat[t, h, :] = W_UK[h]^T q^C[t, h, :] in fp16, for `chunks` chunks of 128
 // tokens of one head per work-group (4 waves of 32 tokens; the next chunk's
 // rows load while a chunk computes and stores).  W_UK[h] ([d_h][d_c]
 // row-major, rows padded to 288 bytes, columns in pf_out_row order) is staged
 // in LDS once and read back as the A operand of v_mfma_f32_32x32x16_bf16 with
 // ds_read_b64_tr_b16 (one output column per lane, 4 consecutive rows per
 // read); the query rows come straight from global as the B operand, and the
-// accumulator holds q_lat^T, stored 8 consecutive columns at a time.
+// accumulator holds q_lat^T, stored 8 consecutive columns at a time.  The
+// work-groups past the last head gate the latents (as launches of their own
+// the gating and the sequence map took 5 us each).
 __global__ __launch_bounds__(256) void prefill_absorb_kernel(const uint16_t* __restrict__ q,
                                                              const uint16_t* __restrict__ w_uk,
-                                                             uint16_t* __restrict__ qf, int T) {
+                                                             uint16_t* __restrict__ qf, int T, int chunks,
+                                                             PfGateArgs ga) {
   constexpr int DH = 128, RS = kPfDC + 16, DQin = DH + kPfDR;
   __shared__ __attribute__((aligned(16))) uint16_t wk[DH * RS];
   const int hh = blockIdx.y;
-  const int c0 = blockIdx.x * kPfSideChunks;
-  const int nch = min(kPfSideChunks, (T + kPfUvTokens - 1) / kPfUvTokens - c0);
+  if (hh >= kPfHeads) {
+    prefill_gate_part(ga, T, (hh - kPfHeads) * gridDim.x + blockIdx.x, kPfGateRows * gridDim.x);
+    return;
+  }
+  const int c0 = blockIdx.x * chunks;
+  const int nch = min(chunks, (T + kPfUvTokens - 1) / kPfUvTokens - c0);
   const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, r32 = lane & 31, h = lane >> 5;
   const int r16 = lane & 15, R1 = (lane >> 4) & 1;
   // a chunk's operand: the lane's token's q^C (B operand)
@@ -432,7 +448,7 @@ __global__ __launch_bounds__(256) void prefill_absorb_kernel(const uint16_t* __r
   }
 }
 
-// out[t, h, :] = W_UV[h] o_lat[t, h, :] for up to 4 chunks of 128 tokens of
+// out[t, h, :] = W_UV[h] o_lat[t, h, :] for `chunks` chunks of 128 tokens of
 // one head per work-group (4 waves of 32 tokens; the next chunk's rows load
 // while a chunk is stored): W_UV[h] ([d_v][d_c], rows padded by 16 bytes)
 // converted to fp16 (exact for magnitudes between 2^-14 and 65504; smaller
@@ -442,12 +458,12 @@ __global__ __launch_bounds__(256) void prefill_absorb_kernel(const uint16_t* __r
 // pf_out_row order), stored 8 consecutive v at a time.
 __global__ __launch_bounds__(256) void prefill_uv_kernel(const uint16_t* __restrict__ olat,
                                                          const uint16_t* __restrict__ w_uv,
-                                                         uint16_t* __restrict__ out, int T) {
+                                                         uint16_t* __restrict__ out, int T, int chunks) {
   constexpr int DV = 128, RS = kPfDC + 8;
   __shared__ __attribute__((aligned(16))) uint16_t wl[DV * RS];
   const int hh = blockIdx.y;
-  const int c0 = blockIdx.x * kPfSideChunks;
-  const int nch = min(kPfSideChunks, (T + kPfUvTokens - 1) / kPfUvTokens - c0);
+  const int c0 = blockIdx.x * chunks;
+  const int nch = min(chunks, (T + kPfUvTokens - 1) / kPfUvTokens - c0);
   const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, r32 = lane & 31, h = lane >> 5;
   f16x8_t ov[kPfDC / 16];  // the lane's token's o_lat, dims 16 c + 8 h .. + 7
   auto load = [&](int chunk) {

@@ -164,3 +164,32 @@ def test_prefill_varlen_explicit_long_sequence_sampled(gpu):
                      rope_dim=wl.rope_dim, storage="bf16", page_table=np.zeros((len(rows), T // 64), np.int32)
                      + np.arange(T // 64, dtype=np.int32)[None, :], page_size=64, max_pages=T // 64)
     assert_close(got[rows], ref, "bf16", "prefill varlen explicit T=4096 sampled")
+
+
+@pytest.mark.parametrize("n,length", [(129, 64), (128, 128)], ids=["t8256", "t16384"])
+def test_prefill_varlen_chunks_per_group(gpu, n, length):
+    # 8256 tokens: two chunks of 128 per side work-group, the last one a partial chunk alone;
+    # 16384: four.  Sequences sampled for the oracle
+    pb = W.generate_prefill_batch(LAYER, [length] * n, seed=90)
+    say(f"prefill_varlen {n} x {length}")
+    got = run_varlen(pb)
+    for b in (0, 1, n // 2, n - 1):
+        s = pb.sequence(b)
+        ref = orc.prefill(s.q, s.latent, s.token_ids, s.gate_table, s.w_uk, s.w_uv, latent_dim=LAYER.latent_dim,
+                          head_dim=LAYER.head_dim, rope_dim=LAYER.rope_dim, storage=LAYER.dtype)
+        a = int(pb.cu_seqlens[b])
+        assert_close(got[a:a + length], ref, "bf16", f"prefill varlen chunks, sequence {b}")
+
+
+@pytest.mark.parametrize("heads,lens", [
+    (9, [130, 5]),            # head by head
+    (24, [257]),              # three heads of an XCD in one group
+    (40, [64, 1, 129]),       # five
+    (64, [200]),              # eight
+    (72, [128, 128]),         # nine heads of an XCD in groups of three
+])
+def test_prefill_varlen_explicit_head_groups(gpu, heads, lens):
+    wl = LAYER.replace(heads=heads, latent_dim=64, gate_dim=64, vocab=2000)
+    pb = W.generate_prefill_batch(wl, lens, seed=91)
+    say(f"prefill_varlen explicit H={heads} lens={lens}")
+    assert_close(run_varlen(pb), oracle_varlen(pb), "bf16", f"prefill varlen explicit H={heads}")
