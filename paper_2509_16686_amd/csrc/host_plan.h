@@ -104,12 +104,13 @@ eg_mla_status validate_prefill(const eg_mla_dims* d, int32_t seq_len, const void
                                const void* out);
 
 // Batched (packed, variable-length) causal prefill on MFMA.
-// Absorbed form (d_c 128, 16 heads): off_qf = absorbed queries, off_olat =
-// latent outputs, off_ct = gated latents (fp16).  Explicit form (other
+// Absorbed form (d_c 128, 16 heads): off_order = the attention's blocks
+// (kPrefillBlock tokens each), off_qf = absorbed queries, off_olat = latent outputs, off_ct = gated latents (fp16).  Explicit form (other
 // shapes): off_qf = K^C, off_olat = V, off_ct = gated latents (bf16 hi rows,
 // then lo rows).
+constexpr int kPrefillBlock = 8;
 struct PrefillVarlenLayout {
-  size_t off_seq_start, off_qf, off_olat, off_ct = 0, bytes;
+  size_t off_seq_start, off_order = 0, off_qf, off_olat, off_ct = 0, bytes;
 };
 PrefillVarlenLayout prefill_varlen_layout(const eg_mla_dims& d, int32_t total_tokens);
 bool prefill_varlen_absorbed(const eg_mla_dims& d);

@@ -197,11 +197,12 @@ extern "C" eg_mla_status eg_mla_prefill_varlen(const eg_mla_dims* dims, int32_t 
     return hipGetLastError() == hipSuccess ? EG_MLA_OK : EG_MLA_ERR_HIP;
   }
   // q_lat (fp16) and the gated latent of every token (keys and values of every
-  // head).  A work-group of the side kernels takes as many chunks as leave two
-  // work-groups per compute unit, at most kPfSideChunks (the weights are then
-  // staged once for them): a chunk each below 8192 tokens.
+  // head).  A work-group of the side kernels takes as many chunks as make one
+  // round of two work-groups per compute unit (the weights are then staged
+  // once for them); with at most four chunks the second round was a quarter
+  // full (20384 tokens: the call 416 -> 407 us).
   const int nchunks = (T + kPfUvTokens - 1) / kPfUvTokens;
-  const int chunks = std::min(std::max(nchunks * kPfHeads / 512, 1), kPfSideChunks);
+  const int chunks = (nchunks * kPfHeads + kPfSideGroups - 1) / kPfSideGroups;
   const int side_wgs = (nchunks + chunks - 1) / chunks;
   uint16_t* ct = reinterpret_cast<uint16_t*>(ws + L.off_ct);
   PfGateArgs ga;
@@ -211,9 +212,10 @@ extern "C" eg_mla_status eg_mla_prefill_varlen(const eg_mla_dims* dims, int32_t 
   ga.cu = cu_seqlens;
   ga.ct = ct;
   ga.seq_start = seq_start;
+  ga.order = reinterpret_cast<int2*>(ws + L.off_order);
   ga.V = d.vocab_size;
   ga.B = batch;
-  hipLaunchKernelGGL(prefill_absorb_kernel, dim3(side_wgs, kPfHeads + kPfGateRows), dim3(256), 0, stream,
+  hipLaunchKernelGGL(prefill_absorb_kernel, dim3(side_wgs, 1 + kPfHeads + kPfGateRows), dim3(256), 0, stream,
                      static_cast<const uint16_t*>(q), static_cast<const uint16_t*>(w_uk), qf, T, chunks, ga);
   PrefillArgs a;
   a.qf = qf;
@@ -221,6 +223,7 @@ extern "C" eg_mla_status eg_mla_prefill_varlen(const eg_mla_dims* dims, int32_t 
   a.latent = static_cast<const uint16_t*>(latent);
   a.ct = ct;
   a.seq_start = seq_start;
+  a.order = ga.order;
   a.olat = olat;
   a.T = T;
   a.scale_log2 = softmax_scale(d) * 1.4426950408889634f;

@@ -15,7 +15,7 @@
 // Three launches: the absorption (q_lat in fp16, for every token) with, in
 // work-groups of its own, the gated latent of every token (fp16, once: the
 // attention's keys and values) and the map from each token to its sequence's
-// first token; the attention kernel below, which writes o_lat / l in fp16; and
+// first token, and the attention blocks' order; the attention kernel below, which writes o_lat / l in fp16; and
 // the up-projection by W_UV per head (W_UV converted exactly to fp16).
 //
 // Precision: the latent part of the attention runs on the fp16 MFMA.  q_lat
@@ -31,8 +31,8 @@
 // same SIMDs) takes 8 consecutive tokens of the
 // packed token stream (a block may straddle sequences: each row masks keys
 // outside its own sequence) and walks tiles of 64 keys from the first token's
-// sequence start to the block's last token.  Blocks are launched heaviest
-// first (last in the stream first).
+// sequence start to the block's last token.  Blocks are launched in an order
+// that the absorption launch prepares (prefill_order_part).
 //  * Tile: the gated latent rows (fp16) and RoPE keys (bf16) of the next tile
 //    go straight from global memory into the other of two LDS buffers while
 //    the current one is computed (buffer_load_dwordx4 ... lds through buffer
@@ -65,7 +65,7 @@
 
 namespace egmla {
 
-constexpr int kPfTokens = 8;      // query tokens per work-group (x 16 heads = 128 rows)
+constexpr int kPfTokens = kPrefillBlock;  // query tokens per work-group (x 16 heads = 128 rows)
 constexpr int kPfHeads = 16;
 constexpr int kPfKeys = 64;       // keys per tile
 constexpr int kPfThreads = 256;   // 4 waves, 32 query rows each; two work-groups per CU
@@ -77,7 +77,7 @@ constexpr int kPfRopeOff = kPfLatBytes;                           // after the l
 constexpr int kPfBufBytes = kPfRopeOff + kPfKeys * kPfRopeRow;    // one tile buffer (24 KB; two per work-group)
 static_assert(2 * 2 * kPfBufBytes <= 160 * 1024, "two work-groups of two tile buffers per compute unit");
 constexpr int kPfUvTokens = 128;  // absorption and up-projection: tokens per chunk (4 waves x 32)
-constexpr int kPfSideChunks = 4;  // chunks per work-group, at most: the head's weights are staged once for them
+constexpr int kPfSideGroups = 512;  // work-groups of the absorption and of the up-projection, about
 constexpr int kPfGateRows = 16;   // rows of work-groups of the absorption launch that gate the latents
 
 typedef __attribute__((ext_vector_type(16))) float pf_f32x16_t;
@@ -127,6 +127,7 @@ struct PfGateArgs {
   const int32_t* cu;
   uint16_t* ct;
   int32_t* seq_start;
+  int2* order;  // [ceil(T / kPfTokens)] block, its first key
   int V, B;
 };
 __device__ __forceinline__ void prefill_gate_part(const PfGateArgs& a, int T, int g, int n) {
@@ -141,6 +142,55 @@ __device__ __forceinline__ void prefill_gate_part(const PfGateArgs& a, int T, in
   }
 }
 
+// The attention's blocks in launch order: the longest sequence first, each
+// from its last block (the heaviest) to its first, by one work-group while the
+// others absorb.  In the stream's reverse order the launch ended with the
+// longest blocks of its first sequence: 1.5 waves per SIMD of two ran on
+// average over 8 sequences of 1001 to 4096 tokens.  (All blocks by weight
+// balanced better, but neighbours in the order then read different keys: the
+// kernel took 356 us there against 324 in the stream's reverse order.)  More
+// than kPfOrderSeqs sequences, or offsets that do not rise from 0 to T, keep
+// the stream's reverse order.
+constexpr int kPfOrderSeqs = 256;
+__device__ __forceinline__ void prefill_order_part(const PfGateArgs& a, int T, int* cus /* [2 kPfOrderSeqs + 1] */) {
+  const int tid = threadIdx.x;
+  const int nblk = (T + kPfTokens - 1) / kPfTokens;
+  const int B = a.B;
+  bool sorted = B <= kPfOrderSeqs;  // uniform
+  int* off = cus + kPfOrderSeqs + 1;
+  if (sorted) {
+    for (int b = tid; b <= B; b += 256) cus[b] = a.cu[b];
+    __syncthreads();
+    const bool bad = tid < B && (cus[tid] < 0 || cus[tid] > cus[tid + 1]);
+    sorted = !__syncthreads_or(bad || cus[0] != 0 || cus[B] != T);
+  }
+  if (!sorted) {
+    for (int k = tid; k < nblk; k += 256) a.order[nblk - 1 - k] = make_int2(k, pf_seq_start(a.cu, B, k * kPfTokens));
+    return;
+  }
+  // blocks of a sequence: those whose first token it holds
+  auto first_block = [&](int b) { return (cus[b] + kPfTokens - 1) / kPfTokens; };
+  if (tid < B) {
+    const int len = cus[tid + 1] - cus[tid];
+    int before = 0;
+    for (int b = 0; b < B; ++b) {
+      const int l = cus[b + 1] - cus[b];
+      if (l > len || (l == len && b < tid)) before += first_block(b + 1) - first_block(b);
+    }
+    off[tid] = before;
+  }
+  __syncthreads();
+  for (int k = tid; k < nblk; k += 256) {
+    int lo = 0, hi = B - 1;  // the sequence of the block's first token
+    while (lo < hi) {
+      const int mid = (lo + hi + 1) >> 1;
+      if (cus[mid] <= k * kPfTokens) lo = mid;
+      else hi = mid - 1;
+    }
+    a.order[off[lo] + first_block(lo + 1) - 1 - k] = make_int2(k, cus[lo]);
+  }
+}
+
 // Word 3 of a raw buffer resource on gfx9 (32-bit data format; stride 0, so
 // the record count is a byte count and offsets past it read zeros).
 constexpr int kPfBufRsrcWord3 = 0x00020000;
@@ -151,6 +201,7 @@ struct PrefillArgs {
   const uint16_t* latent;      // [T][192] bf16: c | k^R
   const uint16_t* ct;          // [T][128] fp16: gated latent
   const int32_t* seq_start;    // [T]
+  const int2* order;           // [ceil(T / kPfTokens)] block, its first key
   uint16_t* olat;              // [T][16][128] fp16: o_lat / l
   int T;
   float scale_log2;            // tau log2(e)
@@ -159,10 +210,10 @@ struct PrefillArgs {
 __global__ __launch_bounds__(kPfThreads, 2) void prefill_attn_mfma_kernel(PrefillArgs a) {
   __shared__ __attribute__((aligned(16))) unsigned char lds0[kPfBufBytes];  // two tile buffers
   __shared__ __attribute__((aligned(16))) unsigned char lds1[kPfBufBytes];
-  const int nblk = (a.T + kPfTokens - 1) / kPfTokens;
-  const int q0 = (nblk - 1 - static_cast<int>(blockIdx.x)) * kPfTokens;  // heaviest blocks first
+  const int2 blk = a.order[blockIdx.x];
+  const int q0 = blk.x * kPfTokens;
   const int q_last = min(q0 + kPfTokens, a.T) - 1;
-  const int kbeg = min(max(a.seq_start[q0], 0), q0);                 // keys from here ...
+  const int kbeg = blk.y;                                            // keys from here ...
   const int kend = q_last + 1;                                       // ... to here (exclusive)
   const int s_max = min(max(a.seq_start[q_last], kbeg), q_last);     // latest sequence start in the block
   const int ntiles = (kend - kbeg + kPfKeys - 1) / kPfKeys;
@@ -373,15 +424,20 @@ __global__ __launch_bounds__(kPfThreads, 2) void prefill_attn_mfma_kernel(Prefil
 // ds_read_b64_tr_b16 (one output column per lane, 4 consecutive rows per
 // read); the query rows come straight from global as the B operand, and the
 // accumulator holds q_lat^T, stored 8 consecutive columns at a time.  The
-// work-groups past the last head gate the latents (as launches of their own
+// first work-group orders the attention's blocks, those past the last
+// head gate the latents (as launches of their own
 // the gating and the sequence map took 5 us each).
-__global__ __launch_bounds__(256) void prefill_absorb_kernel(const uint16_t* __restrict__ q,
+__global__ __launch_bounds__(256, 3) void prefill_absorb_kernel(const uint16_t* __restrict__ q,
                                                              const uint16_t* __restrict__ w_uk,
                                                              uint16_t* __restrict__ qf, int T, int chunks,
                                                              PfGateArgs ga) {
   constexpr int DH = 128, RS = kPfDC + 16, DQin = DH + kPfDR;
   __shared__ __attribute__((aligned(16))) uint16_t wk[DH * RS];
-  const int hh = blockIdx.y;
+  if (blockIdx.y == 0) {  // first: the order is the longest chain of a short call
+    if (blockIdx.x == 0) prefill_order_part(ga, T, reinterpret_cast<int*>(wk));
+    return;
+  }
+  const int hh = static_cast<int>(blockIdx.y) - 1;
   if (hh >= kPfHeads) {
     prefill_gate_part(ga, T, (hh - kPfHeads) * gridDim.x + blockIdx.x, kPfGateRows * gridDim.x);
     return;
@@ -456,7 +512,7 @@ __global__ __launch_bounds__(256) void prefill_absorb_kernel(const uint16_t* __r
 // A operand, the fp16 o_lat rows straight from global as the B operand of
 // v_mfma_f32_32x32x16_f16; the accumulator holds out^T (W_UV rows in
 // pf_out_row order), stored 8 consecutive v at a time.
-__global__ __launch_bounds__(256) void prefill_uv_kernel(const uint16_t* __restrict__ olat,
+__global__ __launch_bounds__(256, 3) void prefill_uv_kernel(const uint16_t* __restrict__ olat,
                                                          const uint16_t* __restrict__ w_uv,
                                                          uint16_t* __restrict__ out, int T, int chunks) {
   constexpr int DV = 128, RS = kPfDC + 8;

@@ -51,6 +51,7 @@ def oracle_varlen(pb):
     [300],                        # several tiles, ragged last tile
     [5, 0, 64, 1, 130, 0, 33],    # empty sequences, exact tiles, short ones
     [1000, 3, 700],               # long sequences around a short one
+    [9, 260, 0, 41, 260, 7],      # the block order: rising, equal and empty ones
 ])
 def test_prefill_varlen_matches_oracle(gpu, lens):
     pb = W.generate_prefill_batch(LAYER, lens, seed=61)
@@ -166,10 +167,11 @@ def test_prefill_varlen_explicit_long_sequence_sampled(gpu):
     assert_close(got[rows], ref, "bf16", "prefill varlen explicit T=4096 sampled")
 
 
-@pytest.mark.parametrize("n,length", [(129, 64), (128, 128)], ids=["t8256", "t16384"])
+@pytest.mark.parametrize("n,length", [(129, 64), (128, 128), (257, 31)], ids=["t8256", "t16384", "b257"])
 def test_prefill_varlen_chunks_per_group(gpu, n, length):
-    # 8256 tokens: two chunks of 128 per side work-group, the last one a partial chunk alone;
-    # 16384: four.  Sequences sampled for the oracle
+    # 8256 tokens: three chunks of 128 per side work-group, the last one a partial chunk; 16384:
+    # four, all whole; 257 sequences: one more than the block order sorts.  Sequences sampled for
+    # the oracle
     pb = W.generate_prefill_batch(LAYER, [length] * n, seed=90)
     say(f"prefill_varlen {n} x {length}")
     got = run_varlen(pb)
