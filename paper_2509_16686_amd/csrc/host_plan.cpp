@@ -306,9 +306,11 @@ PrefillVarlenLayout prefill_varlen_layout(const eg_mla_dims& d, int32_t total_to
   PrefillVarlenLayout L;
   L.off_seq_start = 0;  // int32 [T]
   if (prefill_varlen_absorbed(d)) {
-    L.off_order = align_up(T * 4);                                                     // int2 [ceil(T / 8)]
-    L.off_qf = L.off_order + align_up((T + kPrefillBlock - 1) / kPrefillBlock * 8);    // fp16 [T][H][d_c]
-    L.off_olat = L.off_qf + align_up(T * H * static_cast<size_t>(d.latent_dim) * 2);   // fp16 [T][H][d_c]
+    // the size is that of query rows of d_c + d_r, whose RoPE part the attention reads from
+    // the query: the blocks' order lies in the part of them that is left
+    L.off_qf = align_up(T * 4);                                                    // fp16 [T][H][d_c]
+    L.off_order = L.off_qf + align_up(T * H * static_cast<size_t>(d.latent_dim) * 2);  // int2 [ceil(T / 8)]
+    L.off_olat = L.off_qf + align_up(T * H * static_cast<size_t>(d.latent_dim + d.rope_dim) * 2);  // fp16 [T][H][d_c]
     L.off_ct = L.off_olat + align_up(T * H * static_cast<size_t>(d.latent_dim) * 2);   // fp16 [T][d_c]
     L.bytes = std::max<size_t>(L.off_ct + align_up(T * static_cast<size_t>(d.latent_dim) * 2), kAlign);
   } else {
