@@ -385,45 +385,68 @@ __global__ __launch_bounds__(256) void append_slice_kernel(const uint16_t* __res
 
 // Pass 1 for many tokens: the same partial sums from an LDS-tiled product.
 // Work-group (ks, tt, ot) takes tokens 128 tt .. + 127 and outputs
-// 192 ot .. + 191 over slice ks, in steps of 32 k: each step's 128 token rows
-// and 192 W_DKV rows (64 B each) are staged in LDS (row stride 80 B, so that
+// 192 ot .. + 191 over slice ks, in steps of 32 KG k: each step's 128 token
+// rows and 192 W_DKV rows are staged in LDS (row stride 80 or 144 B, so that
 // the operand reads of 16 rows by 16 lanes hit 64 distinct banks), double
 // buffered, with the global loads two steps ahead in registers.  Wave
-// (wt, wo) = (w % 2, w / 2) forms tokens 64 wt .. + 63 x outputs 96 wo .. + 95
-// as 2 x 3 tiles of v_mfma_f32_32x32x16_bf16 (A: W_DKV rows, B: token rows).
-constexpr int kGemmTok = 128, kGemmOut = 192, kGemmK = 32, kGemmStride = kGemmK + 8;
+// (wt, wo) = (w % 2, w / 2) of each of the KG groups of 4 forms tokens
+// 64 wt .. + 63 x outputs 96 wo .. + 95 as 2 x 3 tiles of
+// v_mfma_f32_32x32x16_bf16 (A: W_DKV rows, B: token rows); group kg takes 32 of
+// a step's k, and two groups add up in LDS at the end.
+// What bounds it: a step is a chain of operand reads, 12 products per wave, LDS
+// writes and a barrier (about 1100 cycles, 384 of them products), with one
+// work-group per compute unit.  KG = 2 puts two waves on a SIMD and reads whole
+// 128-byte lines; at d_c 512, hidden 7168 the call went from 55.9 to 48.4 us at
+// 4096 tokens, 98.5 to 83.9 at 8192, 34.2 to 31.6 at 2048.  The d_c 128 layer's
+// slices are 1 to 4 steps long there, and the addition costs more than that
+// gains (1024 tokens 15.3 us with KG = 1, 15.9 with 2).  Cutting the work into
+// equal runs across tiles instead of slices (one per compute unit) lost more to
+// W_DKV falling out of the L2 than it gained in balance: 74 us at 4096 tokens.
+constexpr int kGemmTok = 128, kGemmOut = 192;
 constexpr int kGemmRows = kGemmTok + kGemmOut;
-constexpr int kGemmLoads = kGemmRows * (kGemmK / 8) / 256;  // 16-byte copies per thread and step
-static_assert(kGemmRows * (kGemmK / 8) % 256 == 0, "whole copies per thread");
+template <int KG>
+struct GemmCfg {
+  static constexpr int K = 32 * KG, STRIDE = K + 8;  // per step; 16-bit elements per staged row
+  static constexpr int THREADS = 256 * KG, PIECES = K / 8;
+  static constexpr int LOADS = kGemmRows * PIECES / THREADS;  // 16-byte copies per thread and step
+  static_assert(kGemmRows * PIECES % THREADS == 0, "whole copies per thread");
+  static constexpr int STAGE_BYTES = 2 * kGemmRows * STRIDE * 2;
+  static constexpr int SUM_BYTES = KG > 1 ? KG * 4 * 12 * 64 * 16 : 0;  // half of each wave's accumulators
+  static constexpr int LDS = STAGE_BYTES > SUM_BYTES ? STAGE_BYTES : SUM_BYTES;
+};
 
-template <int DQ>
-__global__ __launch_bounds__(256, 2) void append_gemm_kernel(const uint16_t* __restrict__ x,
-                                                            const uint16_t* __restrict__ w_dkv,
-                                                            float* __restrict__ part, int n, int hidden, int slice) {
-  __shared__ __attribute__((aligned(16))) uint16_t stage[2][kGemmRows * kGemmStride];
+template <int DQ, int KG>
+__global__ __launch_bounds__(256 * KG, 2) void append_gemm_kernel(const uint16_t* __restrict__ x,
+                                                                  const uint16_t* __restrict__ w_dkv,
+                                                                  float* __restrict__ part, int n, int hidden,
+                                                                  int slice) {
+  using C = GemmCfg<KG>;
+  __shared__ __attribute__((aligned(16))) unsigned char lds[C::LDS];
+  uint16_t(*stage)[kGemmRows * C::STRIDE] = reinterpret_cast<uint16_t(*)[kGemmRows * C::STRIDE]>(lds);
   const int ks = blockIdx.x, tt = blockIdx.y, ot = blockIdx.z;
-  const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, r32 = lane & 31, h = lane >> 5;
+  const int tid = threadIdx.x, lane = tid & 63, r32 = lane & 31, h = lane >> 5;
+  const int w8 = __builtin_amdgcn_readfirstlane(tid >> 6), w = w8 & 3, kg = w8 >> 2;
   const int wt = w & 1, wo = w >> 1;
   const int64_t kb = static_cast<int64_t>(slice) * ks;
-  // copy j = tid + 256 i: row j / 4 (token rows first, then W_DKV rows), 16 bytes at 8 (j % 4)
-  const uint16_t* src[kGemmLoads];
-  int dst[kGemmLoads];
+  // copy j = tid + THREADS i: row j / PIECES (token rows first, then W_DKV rows), 16 bytes at 8 (j % PIECES)
+  const uint16_t* src[C::LOADS];
+  int dst[C::LOADS];
 #pragma unroll
-  for (int i = 0; i < kGemmLoads; ++i) {
-    const int j = tid + 256 * i, row = j >> 2, c = j & 3;
+  for (int i = 0; i < C::LOADS; ++i) {
+    const int j = tid + C::THREADS * i, row = j / C::PIECES, c = j % C::PIECES;
     src[i] = row < kGemmTok ? x + static_cast<int64_t>(min(kGemmTok * tt + row, n - 1)) * hidden + kb + 8 * c
                             : w_dkv + static_cast<int64_t>(kGemmOut * ot + row - kGemmTok) * hidden + kb + 8 * c;
-    dst[i] = row * kGemmStride + 8 * c;
+    dst[i] = row * C::STRIDE + 8 * c;
   }
-  bf16x8_t g[2][kGemmLoads];
+  bf16x8_t g[2][C::LOADS];
   auto fetch = [&](int set, int step) {
 #pragma unroll
-    for (int i = 0; i < kGemmLoads; ++i)
-      g[set][i] = *reinterpret_cast<const bf16x8_t*>(src[i] + static_cast<int64_t>(kGemmK) * step);
+    for (int i = 0; i < C::LOADS; ++i)
+      g[set][i] = *reinterpret_cast<const bf16x8_t*>(src[i] + static_cast<int64_t>(C::K) * step);
   };
   auto put = [&](int buf, int set) {
 #pragma unroll
-    for (int i = 0; i < kGemmLoads; ++i) *reinterpret_cast<bf16x8_t*>(&stage[buf][dst[i]]) = g[set][i];
+    for (int i = 0; i < C::LOADS; ++i) *reinterpret_cast<bf16x8_t*>(&stage[buf][dst[i]]) = g[set][i];
   };
   app_f32x16_t acc[2][3];
 #pragma unroll
@@ -432,18 +455,18 @@ __global__ __launch_bounds__(256, 2) void append_gemm_kernel(const uint16_t* __r
     for (int ob = 0; ob < 3; ++ob)
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[tb][ob][r] = 0.f;
-  const int brow = (64 * wt + r32) * kGemmStride + 8 * h;
-  const int arow = (kGemmTok + 96 * wo + r32) * kGemmStride + 8 * h;
+  const int brow = (64 * wt + r32) * C::STRIDE + 8 * h + 32 * kg;
+  const int arow = (kGemmTok + 96 * wo + r32) * C::STRIDE + 8 * h + 32 * kg;
   auto compute = [&](int buf) {
 #pragma unroll
-    for (int kk = 0; kk < kGemmK / 16; ++kk) {
+    for (int kk = 0; kk < 2; ++kk) {
       bf16x8_t bv[2], av[3];
 #pragma unroll
       for (int tb = 0; tb < 2; ++tb)
-        bv[tb] = *reinterpret_cast<const bf16x8_t*>(&stage[buf][brow + 32 * tb * kGemmStride + 16 * kk]);
+        bv[tb] = *reinterpret_cast<const bf16x8_t*>(&stage[buf][brow + 32 * tb * C::STRIDE + 16 * kk]);
 #pragma unroll
       for (int ob = 0; ob < 3; ++ob)
-        av[ob] = *reinterpret_cast<const bf16x8_t*>(&stage[buf][arow + 32 * ob * kGemmStride + 16 * kk]);
+        av[ob] = *reinterpret_cast<const bf16x8_t*>(&stage[buf][arow + 32 * ob * C::STRIDE + 16 * kk]);
 #pragma unroll
       for (int tb = 0; tb < 2; ++tb)
 #pragma unroll
@@ -458,7 +481,7 @@ __global__ __launch_bounds__(256, 2) void append_gemm_kernel(const uint16_t* __r
   // fetched and written again, to a buffer nothing reads), so that each write
   // to LDS waits only for its own set's loads while the newer set stays in
   // flight.
-  const int steps = slice / kGemmK;
+  const int steps = slice / C::K;
   fetch(0, 0);
   fetch(1, 1);
   put(0, 0);
@@ -475,17 +498,39 @@ __global__ __launch_bounds__(256, 2) void append_gemm_kernel(const uint16_t* __r
     __syncthreads();
   }
   // lane holds outputs (96 wo + 32 ob) + 8 q + 4 h + (0..3) of token 64 wt + 32 tb + r32 in acc[tb][ob][4 q + (0..3)]
-#pragma unroll
-  for (int tb = 0; tb < 2; ++tb) {
+  auto store = [&](int tb, const app_f32x16_t(&a)[3], auto other) {
     const int tok = kGemmTok * tt + 64 * wt + 32 * tb + r32;
-    if (tok >= n) break;
+    if (tok >= n) return;
     float* row = part + (static_cast<int64_t>(ks) * n + tok) * DQ + kGemmOut * ot + 96 * wo + 4 * h;
 #pragma unroll
     for (int ob = 0; ob < 3; ++ob)
 #pragma unroll
       for (int q = 0; q < 4; ++q)
-        *reinterpret_cast<float4*>(row + 32 * ob + 8 * q) =
-            make_float4(acc[tb][ob][4 * q], acc[tb][ob][4 * q + 1], acc[tb][ob][4 * q + 2], acc[tb][ob][4 * q + 3]);
+        *reinterpret_cast<f32x4_t*>(row + 32 * ob + 8 * q) =
+            f32x4_t{a[ob][4 * q], a[ob][4 * q + 1], a[ob][4 * q + 2], a[ob][4 * q + 3]} + other(4 * ob + q);
+  };
+  if constexpr (KG == 1) {
+    auto none = [](int) { return f32x4_t{0.f, 0.f, 0.f, 0.f}; };
+    store(0, acc[0], none);
+    store(1, acc[1], none);
+  } else {
+    // group kg stores token block kg of its tile and hands the other one over
+    // (the stage is free: the loop ended in a barrier)
+    f32x4_t* sum = reinterpret_cast<f32x4_t*>(lds);
+    auto give = [&](const app_f32x16_t(&a)[3]) {
+#pragma unroll
+      for (int ob = 0; ob < 3; ++ob)
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          sum[(12 * w8 + 4 * ob + q) * 64 + lane] =
+              f32x4_t{a[ob][4 * q], a[ob][4 * q + 1], a[ob][4 * q + 2], a[ob][4 * q + 3]};
+    };
+    if (kg == 0) give(acc[1]);
+    else give(acc[0]);
+    __syncthreads();
+    auto given = [&](int i) { return sum[(12 * (w8 ^ 4) + i) * 64 + lane]; };
+    if (kg == 0) store(0, acc[0], given);
+    else store(1, acc[1], given);
   }
 }
 
@@ -717,19 +762,21 @@ extern "C" eg_mla_status eg_mla_append_ws(const eg_mla_dims* dims, int32_t n_tok
   const int per = append_split_tokens(d, n_tokens);
   const bool gemm = append_split_gemm(d, n_tokens);
   const dim3 grid1(nks, (n_tokens + per - 1) / per, (d.latent_dim + d.rope_dim) / (gemm ? kGemmOut : 32));
-  auto pass1 = [&](auto kernel) {
-    hipLaunchKernelGGL(kernel, grid1, dim3(256), 0, stream, xb, wb, part, n_tokens, hidden, slice);
+  auto pass1 = [&](auto kernel, int threads) {
+    hipLaunchKernelGGL(kernel, grid1, dim3(threads), 0, stream, xb, wb, part, n_tokens, hidden, slice);
   };
   if (d.latent_dim == 128) {
-    if (gemm) pass1(append_gemm_kernel<192>);
-    else if (per == 32) pass1(append_slice_kernel<192, 1>);
-    else pass1(append_slice_kernel<192, 2>);
+    if (gemm) pass1(append_gemm_kernel<192, 1>, GemmCfg<1>::THREADS);
+    else if (per == 32) pass1(append_slice_kernel<192, 1>, 256);
+    else pass1(append_slice_kernel<192, 2>, 256);
     hipLaunchKernelGGL((append_finish_kernel<128, 64, 64>), dim3((n_tokens + 3) / 4), dim3(256), 0, stream, part,
                        nks, token_ids, positions, slots, nw, theta, cb, token_id_cache, num_slots, n_tokens);
   } else {
-    if (gemm) pass1(append_gemm_kernel<576>);
-    else if (per == 32) pass1(append_slice_kernel<576, 1>);
-    else pass1(append_slice_kernel<576, 2>);
+    // slices of one unit (few tokens) are too short for two groups: 256 tokens 19.2 us with one, 20.0 with two
+    if (gemm && slice > kAppSliceUnit) pass1(append_gemm_kernel<576, 2>, GemmCfg<2>::THREADS);
+    else if (gemm) pass1(append_gemm_kernel<576, 1>, GemmCfg<1>::THREADS);
+    else if (per == 32) pass1(append_slice_kernel<576, 1>, 256);
+    else pass1(append_slice_kernel<576, 2>, 256);
     // pass 2: a wave per token when the slices are few (4 tokens per
     // work-group), a work-group per token (one pair per thread) when many
     if (nks <= kAppFinishWaveSlices)

@@ -160,3 +160,26 @@ def test_append_token_counts(gpu, wi, entry, n):
     got = B.out_to_f64(cache)[ap.slots]
     assert np.all(np.abs(got - ref) <= 2.0 ** -7 * np.abs(ref) + 1e-5), float(np.max(np.abs(got - ref)))
     np.testing.assert_array_equal(idc.cpu().numpy()[ap.slots], ap.token_ids)
+
+
+@pytest.mark.parametrize("hidden,n", [
+    (256, 256),      # one unit of 256 k: one group
+    (512, 11009),    # the shortest slice of two groups; a ragged last tile of one token
+    (1792, 5505),    # seven units in one slice
+])
+def test_append_two_group_product(gpu, hidden, n):
+    # the d_c 512 layer's tiled product (two groups of waves share a tile's k) at other widths
+    wl = W.WORKLOADS[4].replace(hidden=hidden)
+    ap = W.generate_append(wl, n, n, with_norm=True, seed=92 + n)
+    dims = B.dims_for(wl)
+    cache = torch.zeros((n, wl.row_dim), dtype=torch.bfloat16, device="cuda")
+    idc = torch.full((n,), -7, dtype=torch.int32, device="cuda")
+    say(f"append_ws two groups hidden={hidden} n={n}")
+    run_append("append_ws", dims, stage(ap.x, "bf16"), stage(ap.token_ids, "int"), stage(ap.positions, "int"),
+               stage(ap.slots, "int"), stage(ap.w_dkv, "bf16"), stage(ap.kv_norm_w, "bf16"), cache, idc)
+    torch.cuda.synchronize()
+    ref = orc.append(ap.x, ap.w_dkv, ap.kv_norm_w, ap.positions, latent_dim=wl.latent_dim, rope_dim=wl.rope_dim,
+                     storage="bf16")
+    got = B.out_to_f64(cache)[ap.slots]
+    assert np.all(np.abs(got - ref) <= 2.0 ** -7 * np.abs(ref) + 1e-5), float(np.max(np.abs(got - ref)))
+    np.testing.assert_array_equal(idc.cpu().numpy()[ap.slots], ap.token_ids)
