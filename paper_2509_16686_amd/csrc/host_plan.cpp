@@ -18,8 +18,21 @@ constexpr int kTargetWorkItemsTok = 256;
 // (1 x 32768: 18.7 us with 128 partials, 19.8 with 256).
 constexpr int kMaxPartialsTok = 128;
 constexpr int kMinSplitTok = 64;
-// Smallest capacity for which the d_c 128 kernel takes the balanced schedule.
+// The d_c 128 kernel takes the balanced schedule from this capacity on, where a
+// (sequence, split) item is long enough to pay for the schedule (about 2 us):
+// from kTokBalancedUneven tokens if the items do not fit one per compute unit
+// (some then run two, and the balanced pieces win at equal lengths too), else
+// only from kTokBalancedEven, where the longest sequences set the time.
+// Measured, us per call without / with, lengths n / 16 to n and all n:
+//   72 x 1900 (544-token items, 288 of them)  30.2 / 26.7, 33.4 / 31.5
+//   200 x 1900 (two items a sequence, 400)    55.4 / 38.1, 60.6 / 52.5
+//   96 x 1000 (384, 288)                      25.2 / 21.8, 27.4 / 28.5
+//   64 x 4000 (1024, 256)                     30.5 / 30.4, 36.4 / 37.6
+//   128 x 1000 (512, 256)                     23.5 / 26.0, 26.5 / 28.4
+//   256 x 1900 (1920, 256)                    47.0 / 43.1, 57.6 / 58.2
 constexpr int kTokBalancedMinCap = 1024;
+constexpr int kTokBalancedUneven = 448;
+constexpr int kTokBalancedEven = 1920;
 // fp32 matrix-core kernel: 4-wave work-groups, two per compute unit up to
 // d_c 64; above, a work-group's LDS leaves room for one (measured at batch 32,
 // d_c 256, lengths to 3003: 384-token splits 42.0 us per call, 192-token 48.7).
@@ -127,6 +140,12 @@ eg_mla_status make_decode_plan(const eg_mla_dims& d, int32_t batch, int32_t max_
                                                                      : 128;
     s = std::max<int64_t>(s, min_split);
     if (unit_kernel) s = std::max<int64_t>(s, (p.capacity / kMaxPartialsTok + kTile - 1) / kTile * kTile);
+    // short splits only where the items still run one per compute unit (48 x
+    // 1000: 288 items of 192 tokens 18.8 us per call, 192 of 256 17.1)
+    if (sliced_kernel && unit_kernel && s < 256 &&
+        static_cast<int64_t>(std::max(batch, 1)) * p.head_groups * ceil_div(std::max(p.capacity, 1), static_cast<int>(s)) >
+            kTargetWorkItemsTok)
+      s = 256;
     s = std::min<int64_t>(s, max_split);
     split = static_cast<int>(s);
   }
@@ -189,6 +208,7 @@ eg_mla_status make_decode_plan(const eg_mla_dims& d, int32_t batch, int32_t max_
   // the workspace-free entry's scratch out of it.
   if (sliced_kernel && p.slices == 1 && !p.fused_absorb && d.head_dim == 128 && batch > 32 && p.s_max < 8 &&
       (plan == nullptr || plan->split_tokens == 0) && p.capacity >= kTokBalancedMinCap &&
+      p.split_tokens >= (nblk > kTargetWorkItemsTok ? kTokBalancedUneven : kTokBalancedEven) &&
       batch <= kTokMaxBatch) {
     const int pieces = kTokMaxPieces / p.head_groups / 8 * 8;
     if (pieces > batch &&

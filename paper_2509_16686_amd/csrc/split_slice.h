@@ -216,8 +216,7 @@ __device__ __forceinline__ void publish_stamp(const SplitArgs& a, int b, int hg,
 // kernel takes, measured slower: a range over two sequences pays the list,
 // first loads and merge twice in turn.)  256 sequences of 250 to 3901 tokens:
 // the kernel 72.5 -> 56 us; 48 of 250 to 4096: the call 34.1 -> 27.7 us.  The
-// schedule itself adds 1.5 us to the absorption launch, which a batch of equal
-// lengths pays for nothing (64 x 2048: 25.7 -> 27.4 us).
+// schedule itself costs about 2 us, which the plan weighs (make_decode_plan).
 // tok_schedule, run by one more work-group of the absorption launch, writes
 // each piece as (sequence, first token, tokens, 0) and each sequence's (first
 // row, rows).

@@ -27,7 +27,7 @@ def lens_mix(batch, top, seed):
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("batch,heads,top", [
-    (33, 16, 1024),    # the smallest balanced batch and capacity
+    (33, 16, 1024),    # short items: (sequence, split) ones
     (40, 32, 4100),    # two head groups share each piece
     (64, 16, 9000),    # one long sequence: pieces of the search's upper end
     (384, 16, 1100),   # the largest balanced batch
@@ -43,6 +43,22 @@ def test_balanced_schedule(gpu, batch, heads, top):
     assert not got[inp.seq_lens == 0].any()
     # all of one length: every sequence the same number of pieces
     inp = W.generate(wl, seq_lens=np.full(batch, 1024, dtype=np.int32))
+    got = decode(inp)
+    d = got - decode(inp, B.make_plan(B.PATH_MFMA, 256))  # (sequence, split) items
+    assert np.linalg.norm(d) <= 5e-3 * np.linalg.norm(got)  # two bf16 outputs of sums in another order
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("batch,top", [
+    (72, 1600),     # 288 items of 480 tokens: balanced
+    (64, 1728),     # 256 items of 448: not
+    (256, 1920),    # 256 items of 1920: balanced
+])
+def test_balanced_rule(gpu, batch, top):
+    wl = W.WORKLOADS[1].replace(name="balanced", batch=batch, vocab=3000, seq_len=None, seq_len_range=(0, top),
+                                page_size=16, paged=True, seed=7)
+    inp = W.generate(wl, seq_lens=lens_mix(batch, top, batch))
+    say(f"decode balanced rule B={batch} top={top}")
     got = decode(inp)
     d = got - decode(inp, B.make_plan(B.PATH_MFMA, 256))  # (sequence, split) items
     assert np.linalg.norm(d) <= 5e-3 * np.linalg.norm(got)  # two bf16 outputs of sums in another order
