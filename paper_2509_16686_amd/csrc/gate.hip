@@ -123,39 +123,64 @@ __global__ __launch_bounds__(64 * kGateWaves, 1) void gate_rows_mfma_kernel(cons
   const uint16_t* arow = wl + i32 * RS + 8 * h;
   // this work-group's blocks: team, team + nteams, ...; wave w takes every 8th of them
   const int64_t step = static_cast<int64_t>(nteams) * kGateWaves;
-  int64_t rb = team + static_cast<int64_t>(nteams) * w;
+  const int64_t rb_first = team + static_cast<int64_t>(nteams) * w;
+  int64_t rb = rb_first;
   // a block's row ids; past the end of the rows (or of the blocks) the last row
   // repeats, so every load stays in bounds and nothing past n is stored
   auto row_id = [&](int64_t blk) { return clamp_id(ids[min(blk * 32 + i32, n - 1)], V); };
   auto erow_of = [&](int id) { return emb + static_cast<int64_t>(id) * E + 8 * h; };
   constexpr int NH = NC / 2;  // ONE_PASS: E == EP
 
-  // the first block's ids travel while W^UE is staged
   const int id_first = row_id(min(rb, nrb - 1));
-  const int per_row = E / 8;
-  for (int p = tid; p < CB * per_row; p += 64 * kGateWaves) {
-    const int r = p / per_row, k8 = (p % per_row) * 8;
-    u32x4_t v = u32x4_t{0u, 0u, 0u, 0u};
-    if (r < nc) v = *reinterpret_cast<const u32x4_t*>(w_ue + static_cast<int64_t>(c0 + r) * E + k8);
-    *reinterpret_cast<u32x4_t*>(wl + r * RS + k8) = v;
-  }
   bf16x8_t bA[NH], bB[NH];
+  auto load_rows = [&](int id) {
+    const uint16_t* erow = erow_of(id);
+#pragma unroll
+    for (int c = 0; c < NH; ++c) bA[c] = *reinterpret_cast<const bf16x8_t*>(erow + 16 * c);
+#pragma unroll
+    for (int c = 0; c < NH; ++c) bB[c] = *reinterpret_cast<const bf16x8_t*>(erow + 16 * (NH + c));
+  };
+  if constexpr (ONE_PASS) {
+    // W^UE goes to LDS with all its loads, and then the first block's rows, in
+    // flight at once: most waves have one block only (50304 ids: 1572 blocks
+    // for 1600 waves), so the call is this chain of latencies (256 sequences of
+    // 250 to 3901 tokens, table and decode: 97.3 -> 93.8 us)
+    constexpr int PER_ROW = EP / 8, NW = CB * PER_ROW / (64 * kGateWaves);
+    static_assert(CB * PER_ROW % (64 * kGateWaves) == 0, "whole copies per thread");
+    u32x4_t v[NW];
+#pragma unroll
+    for (int i = 0; i < NW; ++i) {
+      const int p = tid + 64 * kGateWaves * i, r = min(p / PER_ROW, nc - 1);
+      v[i] = *reinterpret_cast<const u32x4_t*>(w_ue + static_cast<int64_t>(c0 + r) * E + (p % PER_ROW) * 8);
+    }
+    load_rows(id_first);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int i = 0; i < NW; ++i) {
+      const int p = tid + 64 * kGateWaves * i;
+      *reinterpret_cast<u32x4_t*>(wl + p / PER_ROW * RS + (p % PER_ROW) * 8) = v[i];
+    }
+  } else {
+    const int per_row = E / 8;
+    for (int p = tid; p < CB * per_row; p += 64 * kGateWaves) {
+      const int r = p / per_row, k8 = (p % per_row) * 8;
+      u32x4_t v = u32x4_t{0u, 0u, 0u, 0u};
+      if (r < nc) v = *reinterpret_cast<const u32x4_t*>(w_ue + static_cast<int64_t>(c0 + r) * E + k8);
+      *reinterpret_cast<u32x4_t*>(wl + r * RS + k8) = v;
+    }
+  }
   int id_next = id_first;
   __syncthreads();
 
   if constexpr (ONE_PASS) {
     for (; rb < nrb; rb += step) {
-      const uint16_t* erow = erow_of(id_next);
+      if (rb != rb_first) load_rows(id_next);  // the first block's are there
       const int id_after = row_id(min(rb + step, nrb - 1));
       gate_f32x16_t acc[NCB];
 #pragma unroll
       for (int cb = 0; cb < NCB; ++cb)
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc[cb][r] = 0.f;
-#pragma unroll
-      for (int c = 0; c < NH; ++c) bA[c] = *reinterpret_cast<const bf16x8_t*>(erow + 16 * c);
-#pragma unroll
-      for (int c = 0; c < NH; ++c) bB[c] = *reinterpret_cast<const bf16x8_t*>(erow + 16 * (NH + c));
       __builtin_amdgcn_sched_barrier(0);
       gate_products<NH, NCB>(bA, arow, RS, 0, acc);
       gate_products<NH, NCB>(bB, arow, RS, 16 * NH, acc);
