@@ -203,8 +203,8 @@ eg_mla_status make_decode_plan(const eg_mla_dims& d, int32_t batch, int32_t max_
   // Few splits per sequence: a work-group's time follows its sequence's
   // length, so the d_c 128 kernel takes the balanced schedule, two
   // work-groups per compute unit.  Not beyond the batch where the dispatcher
-  // itself evens out the work-groups, nor where a range could outgrow the
-  // token list, nor where the extra partial rows would take a call that fits
+  // itself evens out the work-groups, nor where the search's largest piece (about
+  // N / (pieces - batch), see tok_sizes) could outgrow the token list, nor where the extra partial rows would take a call that fits
   // the workspace-free entry's scratch out of it.
   if (sliced_kernel && p.slices == 1 && !p.fused_absorb && d.head_dim == 128 && batch > 32 && p.s_max < 8 &&
       (plan == nullptr || plan->split_tokens == 0) && p.capacity >= kTokBalancedMinCap &&

@@ -45,10 +45,12 @@
 // Phase 3.  The waves merge their (max, sum, output) and write the partial.
 #pragma once
 
+#include "tok_pieces.h"
+
 namespace egmla {
 
 // Largest number of positions one work item of the sliced kernel scans.
-constexpr int kMaxScanTokens = 4096;
+constexpr int kMaxScanTokens = kMaxSliceSplitTokens;
 
 template <int DC, int DR, int NW>
 struct SsplitCfg {
@@ -229,7 +231,7 @@ struct TokSchedArgs {
 
 template <int NT>
 __device__ __forceinline__ void tok_schedule(const TokSchedArgs& sa, int B) {
-  static_assert(NT == 256, "64 candidates x 4 quarters of the batch");
+  static_assert(NT == 4 * kTokCandidates, "candidates x 4 quarters of the batch");
   __shared__ int len[kTokMaxBatch];
   __shared__ int pre[kTokMaxBatch + 1];  // pieces before sequence b
   __shared__ int wsum[NT / 64];
@@ -246,39 +248,24 @@ __device__ __forceinline__ void tok_schedule(const TokSchedArgs& sa, int B) {
   if (lane == 0) wsum[w] = v;
   __syncthreads();
   const int N = wsum[0] + wsum[1] + wsum[2] + wsum[3];
-  // candidate piece sizes, multiples of 16: from N / G, below which there
-  // are always more than G pieces, to N / (G - B), which always fits (B < G)
-  const int lo = max(kTokPieceMin, (N / sa.G + 15) & ~15), hi = max(lo, (N / (sa.G - B) + 16) & ~15);
-  const int step = ((hi - lo) / 62 + 16) & ~15;
-  // ceil(L / c), exact for lengths below 2^24
-  auto pieces_of = [](int L, int c, float rc) {
-    const int x = L + c - 1;
-    const int q = static_cast<int>(static_cast<float>(x) * rc);
-    const int r = x - q * c;
-    return q + (r >= c ? 1 : 0) - (r < 0 ? 1 : 0);
-  };
-  // one more candidate (the last lane): a tenth above an even cut into G / 2
-  // pieces; where it makes at most that many, one work-group per compute unit
-  // starts, loads and merges half as often
-  const int half = sa.G / 2;
-  const int even = max(kTokPieceMin, (N / half + N / (10 * half) + 15) & ~15);
+  const TokSizes sizes = tok_sizes(N, sa.G, B);
   {
-    const int c = lane == 63 ? even : lo + step * lane;
+    const int c = tok_candidate(sizes, lane);
     const float rc = 1.f / static_cast<float>(c);
     int k = 0;
 #pragma unroll 8
-    for (int b = w; b < B; b += 4) k += pieces_of(len[b], c, rc);
+    for (int b = w; b < B; b += 4) k += tok_piece_count(len[b], c, rc);
     cnt[tid] = k;
   }
   __syncthreads();
   const int total = cnt[lane] + cnt[64 + lane] + cnt[128 + lane] + cnt[192 + lane];
-  const uint64_t fits = __builtin_amdgcn_ballot_w64(total <= (lane == 63 ? half : sa.G));
-  const int c = (fits >> 63) ? even : lo + step * (fits ? __builtin_ctzll(fits) : 62);
+  const uint64_t fits = __builtin_amdgcn_ballot_w64(total <= tok_candidate_limit(sa.G, lane));
+  const int c = tok_candidate(sizes, tok_choice(fits));
   const float rc = 1.f / static_cast<float>(c);
   int carry = 0;
   for (int base = 0; base < B; base += NT) {
     const int b = base + tid;
-    const int k = b < B ? pieces_of(len[b], c, rc) : 0;
+    const int k = b < B ? tok_piece_count(len[b], c, rc) : 0;
     int x = k;
 #pragma unroll
     for (int o = 1; o < 64; o <<= 1) {
@@ -309,8 +296,8 @@ __device__ __forceinline__ void tok_schedule(const TokSchedArgs& sa, int B) {
         if (pre[mid] <= g) l = mid;
         else h = mid;
       }
-      const int L = len[l], k = pieces_of(L, c, rc);
-      const int size = ((L + k - 1) / k + 15) & ~15;  // at most c, so that the k - 1 first pieces stay below L
+      const int L = len[l], k = tok_piece_count(L, c, rc);
+      const int size = tok_piece_tokens(L, k);
       const int t0 = (g - pre[l]) * size;
       r = make_int4(l, t0, min(size, L - t0), 0);
     }
@@ -344,7 +331,7 @@ __global__ __launch_bounds__(NW * 64, 2) void split_slice_kernel(SplitArgs a) {
     const int4 r = a.tok_pieces[piece];
     b = r.x;
     t0 = r.y;
-    n = r.z;
+    n = min(r.z, kMaxScanTokens);  // (never more: tok_sizes)
     if (n <= 0) return;
   } else {
     L = clamp_len(a.seq_lens[b], a.cap);

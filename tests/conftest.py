@@ -1,4 +1,6 @@
 import os
+import shutil
+import subprocess
 import sys
 
 import pytest
@@ -21,3 +23,21 @@ def gpu():
         pytest.skip("no GPU visible")
     from paper_2509_16686_amd import binding
     return binding.lib()
+
+
+@pytest.fixture(scope="session")
+def tok_pieces(tmp_path_factory):
+    """Runs the host build of the d_c 128 decode's plan and balanced schedule (tok_pieces_host.cpp)."""
+    cxx = shutil.which("g++") or shutil.which("c++")
+    assert cxx, "no C++ compiler"
+    exe = str(tmp_path_factory.mktemp("tok_pieces") / "tok_pieces_host")
+    csrc = os.path.join(ROOT, "paper_2509_16686_amd", "csrc")
+    subprocess.run([cxx, "-O2", "-std=c++17", "-I", os.path.join(ROOT, "include"), "-I", csrc,
+                    os.path.join(ROOT, "tests", "tok_pieces_host.cpp"), os.path.join(csrc, "host_plan.cpp"),
+                    "-o", exe], check=True)
+
+    def run(*args, text=""):
+        r = subprocess.run([exe, *map(str, args)], input=text, capture_output=True, text=True)
+        assert r.returncode == 0, (args, r.stdout, r.stderr)
+        return [tuple(map(int, line.split())) for line in r.stdout.splitlines()]
+    return run

@@ -65,6 +65,44 @@ def test_balanced_rule(gpu, batch, top):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("batch,length,spread", [
+    (60, 20000, 1),      # an even cut into one piece per compute unit would pass the 4096-token list
+    (128, 10000, 1),
+    (48, 24000, 1536),   # lengths 1536 apart at most
+])
+def test_balanced_schedule_long(gpu, tok_pieces, batch, length, spread):
+    """Balanced pieces near the token list's end against (sequence, split) items of 4096 tokens."""
+    import torch
+    lens = length - np.random.default_rng(batch).integers(0, spread, batch)
+    lens[0] = length
+    balanced = tok_pieces("plan", 16, batch, length)[0][0]
+    cut = tok_pieces("cut", 16, batch, length, text=" ".join(map(str, lens)))
+    assert balanced and 1800 < max(t for _, _, t in cut) <= 4096
+    g = torch.Generator(device="cuda")
+    g.manual_seed(11)
+    rnd = lambda *s: torch.randn(*s, generator=g, device="cuda").to(torch.bfloat16)
+    dims = B.make_dims(num_heads=16, head_dim=128, v_head_dim=128, latent_dim=128, rope_dim=64, vocab_size=5000,
+                       page_size=8)
+    pages = length // 8
+    q, cache = rnd(batch, 16, 192), rnd(batch * length, 192)
+    ids = torch.randint(0, 5000, (batch * length,), generator=g, device="cuda", dtype=torch.int32)
+    gate, w_uk, w_uv = rnd(5000, 128), rnd(16, 128, 128) / 11, rnd(16, 128, 128) / 11
+    seq = torch.from_numpy(lens.astype(np.int32)).cuda()
+    outs = []
+    for plan in (None, B.make_plan(B.PATH_MFMA, 4096)):
+        out = torch.full((batch, 16, 128), float("nan"), dtype=torch.bfloat16, device="cuda")
+        dd = B.DeviceDecode(dims=dims, q=q, cache=cache, ids=ids, gate=gate, w_uk=w_uk, w_uv=w_uv, seq_lens=seq,
+                            page_table=None, max_pages=pages, out=out)
+        say(f"decode balanced long B={batch} L={length} plan={'balanced' if plan is None else 4096}")
+        B.run_decode(dd, plan=plan)
+        torch.cuda.synchronize()
+        outs.append(out.double().cpu().numpy())
+    assert np.isfinite(outs[0]).all()
+    # two bf16 outputs of sums in another order: an absorbed query one fp32 sum of 128 products each way
+    assert np.linalg.norm(outs[0] - outs[1]) <= 5e-3 * np.linalg.norm(outs[1])
+
+
+@pytest.mark.gpu
 def test_balanced_schedule_no_tokens(gpu):
     wl = W.WORKLOADS[1].replace(batch=40, vocab=100, seq_len=None, seq_len_range=(0, 1024), page_size=64, paged=True)
     inp = W.generate(wl, seq_lens=np.zeros(40, dtype=np.int32))

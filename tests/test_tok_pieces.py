@@ -1,0 +1,23 @@
+"""Pieces of the d_c 128 decode's balanced schedule, cut on the host by the device's own arithmetic."""
+import pytest
+
+TOKEN_LIST = 4096  # tokens a work-group of the split kernel can list
+
+
+@pytest.mark.parametrize("heads", [16, 32, 48, 64, 96, 128])
+def test_pieces_fit_the_token_list(tok_pieces, heads):
+    """Over every batch and capacity with a balanced schedule: no piece beyond the token list, no more pieces than
+    partial rows, every token in one piece (the program fails otherwise)."""
+    plans, cuts, longest = tok_pieces("sweep", heads)[0]
+    assert plans > 0 and cuts == 7 * plans and longest <= TOKEN_LIST
+
+
+@pytest.mark.parametrize("batch,length", [(40, 25000), (60, 20000), (64, 20000), (62, 28000), (128, 10000),
+                                          (48, 24000), (40, 28672)])
+def test_long_batches(tok_pieces, batch, length):
+    """Where an even cut into one piece per compute unit would be longer than the list."""
+    balanced, pieces = tok_pieces("plan", 16, batch, length)[0][:2]
+    assert balanced and pieces == 512
+    cut = tok_pieces("cut", 16, batch, length, text=f"{length} " * batch)
+    assert len(cut) <= pieces and max(t for _, _, t in cut) <= TOKEN_LIST
+    assert sum(t for _, _, t in cut) == batch * length
