@@ -260,7 +260,8 @@ __global__ __launch_bounds__(kCombWaves * 64) void combine_mfma_kernel(const flo
                                                                        const int32_t* __restrict__ seq_lens,
                                                                        uint16_t* __restrict__ out, int B, int H,
                                                                        int cap, int split, int s_max, int slices,
-                                                                       const int2* __restrict__ seq_rows, int spw) {
+                                                                       const int2* __restrict__ seq_rows, int spw,
+                                                                       Stamps stamps) {
   constexpr int OS = DC + 8;     // bf16 elements per merged row in LDS
   constexpr int PER = DC / 64;  // latent columns per lane
   constexpr int NKC = DC / 32;
@@ -354,6 +355,7 @@ __global__ __launch_bounds__(kCombWaves * 64) void combine_mfma_kernel(const flo
   }
   __syncthreads();
 
+  clear_stamps<kCombWaves * 64>(stamps, H);
   // (4) out^T[vt*16 + 4g + r][b0 + r16] for this wave's tile
   if constexpr (!kEarlyW) load_w();
   if (vt < nvt) {
@@ -540,19 +542,17 @@ __global__ __launch_bounds__(kCombWideWaves * 64) void combine_wide_kernel(const
 // out^T[v][b] = W_UV[h][v][:] . o[b][:] on v_mfma_f32_16x16x32_bf16, wave w
 // taking output tiles w, w + 4, ... of 16 rows, the merged rows as the B
 // operand's first 4 columns (split once into bf16 hi + lo as they go to LDS,
-// a product each).  The W_UV rows are loaded first;
-// `wait(b)` is called by each wave before it loads the partials of its
-// sequence (nothing to wait for in a kernel of its own).
+// a product each).  The W_UV rows are loaded first.
 // ---------------------------------------------------------------------------
 constexpr int kComb4Seq = 4;
 
-template <int DC, int DV, typename Wait>
+template <int DC, int DV>
 __device__ __forceinline__ void combine4_block(const float* __restrict__ part_ml, const float* __restrict__ part_o,
                                                const uint16_t* __restrict__ w_uv,
                                                const int32_t* __restrict__ seq_lens, uint16_t* __restrict__ out,
                                                int B, int H, int cap, int split, int s_max, int slices,
                                                const int2* __restrict__ seq_rows, int h, int b0, uint16_t* o_s,
-                                               Wait wait) {
+                                               const Stamps& stamps) {
   constexpr int OS = DC + 8;  // bf16 elements: o / l hi in rows 0 .. 3, lo in rows 4 .. 7
   constexpr int PER = DC / 64;
   constexpr int NKC = DC / 32;
@@ -591,7 +591,6 @@ __device__ __forceinline__ void combine4_block(const float* __restrict__ part_ml
     float acc[PER];
 #pragma unroll
     for (int j = 0; j < PER; ++j) acc[j] = 0.f;
-    if (w < nseq) wait(b);
     if (ns > 0) {
       const int64_t base = row0 * H + h;
       if (ns <= 8) {
@@ -612,6 +611,7 @@ __device__ __forceinline__ void combine4_block(const float* __restrict__ part_ml
     }
   }
   __syncthreads();
+  clear_stamps<256>(stamps, H);
   // (3) out^T[vt*16 + 4g + r][b0 + r16] for this wave's tiles
 #pragma unroll
   for (int t = 0; t < TPW; ++t) {
@@ -643,10 +643,11 @@ template <int DC, int DV>
 __global__ __launch_bounds__(256) void combine4_kernel(const float* __restrict__ part_ml, const float* __restrict__ part_o,
                                                        const uint16_t* __restrict__ w_uv, const int32_t* __restrict__ seq_lens,
                                                        uint16_t* __restrict__ out, int B, int H, int cap, int split,
-                                                       int s_max, int slices, const int2* __restrict__ seq_rows) {
+                                                       int s_max, int slices, const int2* __restrict__ seq_rows,
+                                                       Stamps stamps) {
   __shared__ __attribute__((aligned(16))) uint16_t o_s[2 * kComb4Seq * (DC + 8)];
   combine4_block<DC, DV>(part_ml, part_o, w_uv, seq_lens, out, B, H, cap, split, s_max, slices, seq_rows, blockIdx.x,
-                         blockIdx.y * kComb4Seq, o_s, [](int) {});
+                         blockIdx.y * kComb4Seq, o_s, stamps);
 }
 
 }  // namespace egmla

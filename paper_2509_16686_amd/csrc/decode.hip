@@ -245,6 +245,23 @@ __global__ __launch_bounds__(kValuThreads) void split_valu_kernel(SplitArgs a) {
 #include "split_f32.h"
 namespace egmla {
 
+// Stamps of the fused absorption, zeroed by the merge (which runs once the
+// split kernel is done with them): the next call on the workspace then waits
+// for its own, also where it is the same launch again, with the same stamp, in
+// a replayed graph.  At most 512 (two work-groups per compute unit), fewer than
+// the merge has threads.  (Before the merge kernels' last products, which
+// cover the stores: at their start, with the grid's size from the dispatch
+// packet, it cost 0.3 us a call, at their end 0.2.)
+struct Stamps {
+  unsigned long long* p;
+  int n;
+};
+template <int THREADS>
+__device__ __forceinline__ void clear_stamps(const Stamps& st, int H) {  // grid (H, ...)
+  const int i = static_cast<int>((blockIdx.y * H + blockIdx.x) * THREADS + threadIdx.x);
+  if (i < st.n) __hip_atomic_store(st.p + i, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 // ---------------------------------------------------------------------------
 // 3. combine: merge the splits of (b, h) and apply W_UV[h].
 // grid (H, B), 256 threads.
@@ -255,7 +272,9 @@ __global__ __launch_bounds__(256) void combine_kernel(const float* __restrict__ 
                                                       const void* __restrict__ w_uv,
                                                       const int32_t* __restrict__ seq_lens, void* __restrict__ out,
                                                       int H, int DC, int DV, int cap, int split, int s_max,
-                                                      int slices, const int2* __restrict__ seq_rows) {
+                                                      int slices, const int2* __restrict__ seq_rows,
+                                                      Stamps stamps) {
+  clear_stamps<256>(stamps, H);
   // s_max splits of `slices` partials each per sequence, or (balanced
   // schedule) the rows seq_rows[b] lists; a partial without tokens has
   // maximum -inf and contributes nothing
@@ -337,7 +356,7 @@ constexpr int kSliceDepth = EGMLA_SLICE_DEPTH;
 template <int DC>
 hipError_t launch_combine_dc(dim3 grid, hipStream_t stream, const float* pm, const float* po, const uint16_t* wv,
                              const int32_t* seq_lens, uint16_t* ov, int B, int H, int cap, int split, int s_max,
-                             int slices, const int2* seq_rows, int spw) {
+                             int slices, const int2* seq_rows, int spw, Stamps stamps) {
   // Small work-groups when every sequence's partials fit one merge batch and
   // the grid stays within two work-groups per compute unit (measured faster
   // there; many partials per sequence, or many work-groups, favour the
@@ -347,7 +366,7 @@ hipError_t launch_combine_dc(dim3 grid, hipStream_t stream, const float* pm, con
   const int64_t small_wg = static_cast<int64_t>(H) * ((B + kComb4Seq - 1) / kComb4Seq);
   if ((seq_rows ? DC == 128 : static_cast<int64_t>(s_max) * slices <= 8) && small_wg <= 512) {
     hipLaunchKernelGGL((combine4_kernel<DC, 128>), dim3(H, (B + kComb4Seq - 1) / kComb4Seq), dim3(256), 0, stream,
-                       pm, po, wv, seq_lens, ov, B, H, cap, split, s_max, slices, seq_rows);
+                       pm, po, wv, seq_lens, ov, B, H, cap, split, s_max, slices, seq_rows, stamps);
     return hipGetLastError();
   }
   const size_t lds = combine_lds_bytes(DC);
@@ -365,21 +384,21 @@ hipError_t launch_combine_dc(dim3 grid, hipStream_t stream, const float* pm, con
   hipError_t e = set_lds(combine_mfma_kernel<DC, 128>, lds);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL((combine_mfma_kernel<DC, 128>), grid, dim3(kCombWaves * 64), lds, stream, pm, po, wv, seq_lens,
-                     ov, B, H, cap, split, s_max, slices, seq_rows, spw);
+                     ov, B, H, cap, split, s_max, slices, seq_rows, spw, stamps);
   return hipGetLastError();
 }
 
 hipError_t launch_combine_mfma(int dc, dim3 grid, hipStream_t stream, const float* pm, const float* po,
                                const uint16_t* wv, const int32_t* seq_lens, uint16_t* ov, int B, int H, int cap,
-                               int split, int s_max, int slices, const int2* seq_rows, int spw) {
+                               int split, int s_max, int slices, const int2* seq_rows, int spw, Stamps stamps) {
   if (dc == 128)
     return launch_combine_dc<128>(grid, stream, pm, po, wv, seq_lens, ov, B, H, cap, split, s_max, slices, seq_rows,
-                                  spw);
+                                  spw, stamps);
   if (dc == 320)
     return launch_combine_dc<320>(grid, stream, pm, po, wv, seq_lens, ov, B, H, cap, split, s_max, slices, seq_rows,
-                                  spw);
+                                  spw, stamps);
   return launch_combine_dc<512>(grid, stream, pm, po, wv, seq_lens, ov, B, H, cap, split, s_max, slices, seq_rows,
-                                spw);
+                                spw, stamps);
 }
 
 }  // namespace
@@ -420,10 +439,11 @@ hipError_t launch_slice(const SplitArgs& a, int slices, int pieces, int nblocks,
 }
 
 // Stamp of a decode call whose split kernel absorbs the query: distinct for
-// every call of the process and never 0, so that no stamp left in a
-// workspace by an earlier call (or found in fresh memory, but for a chance of
-// 2^-64 per stamp) matches.  The first value is drawn from the clock and the
-// address space layout.
+// every call of the process and never 0, so that nothing found in a fresh
+// workspace matches (but for a chance of 2^-64 per stamp).  The merge zeroes a
+// call's stamps (clear_stamps): a captured call replays with the stamp it was
+// captured with.  The first value is drawn from the clock and the address
+// space layout.
 unsigned long long next_stamp() {
   static std::atomic<unsigned long long> counter{
       (static_cast<unsigned long long>(std::chrono::steady_clock::now().time_since_epoch().count()) * 0x9E3779B97F4A7C15ull) ^
@@ -569,6 +589,8 @@ eg_mla_status run_decode(const eg_mla_dims& d, const DecodePlan& p, int32_t batc
   int4* tok_pieces = reinterpret_cast<int4*>(wg_start);
   const SchedArgs sched{{seq_lens, p.capacity, p.balanced ? wide_groups(p.head_groups) : 0, sched_hdr, wg_start, seq_rows},
                         {seq_lens, p.capacity, p.pieces, tok_pieces, seq_rows}};
+  const Stamps stamps{p.fused_absorb ? reinterpret_cast<unsigned long long*>(ws + p.off_flags) : nullptr,
+                      p.fused_absorb ? batch * p.head_groups * p.s_max : 0};
   // 1. absorption (or inside the split kernel)
   if (!p.fused_absorb && !p.one_launch) {
     dim3 grid(d.num_heads, (d.latent_dim + kAbsorbCols - 1) / kAbsorbCols, (batch + kAbsorbRows - 1) / kAbsorbRows);
@@ -667,7 +689,7 @@ eg_mla_status run_decode(const eg_mla_dims& d, const DecodePlan& p, int32_t batc
     if (p.fused_absorb) {
       a.qin = static_cast<const uint16_t*>(q);
       a.w_uk = static_cast<const uint16_t*>(w_uk);
-      a.qflags = reinterpret_cast<unsigned long long*>(ws + p.off_flags);
+      a.qflags = stamps.p;
       a.stamp = next_stamp();
       a.spin_limit = absorb_spin_limit();
     }
@@ -704,18 +726,18 @@ eg_mla_status run_decode(const eg_mla_dims& d, const DecodePlan& p, int32_t batc
       const uint16_t* wv = static_cast<const uint16_t*>(w_uv);
       uint16_t* ov = static_cast<uint16_t*>(out);
       if (launch_combine_mfma(d.latent_dim, g2, stream, pm, po, wv, seq_lens, ov, batch, d.num_heads, p.capacity,
-                              p.split_tokens, p.s_max, p.slices, seq_rows, spw) != hipSuccess)
+                              p.split_tokens, p.s_max, p.slices, seq_rows, spw, stamps) != hipSuccess)
         return EG_MLA_ERR_HIP;
     } else if (bf) {
       if (set_lds(combine_kernel<true>, lds) != hipSuccess) return EG_MLA_ERR_HIP;
       hipLaunchKernelGGL(combine_kernel<true>, grid, dim3(256), lds, stream, part_ml, part_o, w_uv, seq_lens, out,
                          d.num_heads, d.latent_dim, d.v_head_dim, p.capacity, p.split_tokens, p.s_max, p.slices,
-                         seq_rows);
+                         seq_rows, stamps);
     } else {
       if (set_lds(combine_kernel<false>, lds) != hipSuccess) return EG_MLA_ERR_HIP;
       hipLaunchKernelGGL(combine_kernel<false>, grid, dim3(256), lds, stream, part_ml, part_o, w_uv, seq_lens, out,
                          d.num_heads, d.latent_dim, d.v_head_dim, p.capacity, p.split_tokens, p.s_max, p.slices,
-                         seq_rows);
+                         seq_rows, stamps);
     }
     if (hipGetLastError() != hipSuccess) return EG_MLA_ERR_HIP;
   }
