@@ -265,15 +265,16 @@ eg_mla_status eg_mla_gate_rows(const eg_mla_dims* dims, int32_t emb_dim, int32_t
  * computation with each distinct id computed once: eg_mla_decode then takes
  * `table` as its gate table with the step's own token ids
  * (dims->vocab_size = emb_vocab).  On the MFMA path a first kernel lists
- * the distinct ids (bitmaps in `marks`, alternating by the stamp's parity;
- * above 524288 ids an atomic exchange of `stamp` per row); the gate rows are
- * computed over that list only.  Other paths compute every row and store identical bits for
- * repeated ids.
+ * the distinct ids (an atomic exchange of `stamp` per row, or, from
+ * max(65536, emb_vocab) rows and up to 522240 ids, bitmaps in `marks` that
+ * alternate by the stamp's parity); the gate rows are computed over that list
+ * only.  Other paths compute every row and store identical bits for repeated
+ * ids.
  *
  *   emb, w_ue, ids as for eg_mla_gate_rows;  table [emb_vocab, d_c]
  *   marks  device workspace of eg_mla_gate_table_marks_size(dims, emb_dim,
- *          emb_vocab) bytes (a 128-byte line per id for bitmap words or
- *          stamps, two counters, an id list),
+ *          emb_vocab) bytes (a 128-byte line per id for its stamp and
+ *          bitmap words, two counters, an id list),
  *          4-byte aligned, owned by the caller: zero it before the first
  *          call and keep it between calls;
  *   stamp  1 on the first call after the marks were zeroed, then the previous

@@ -34,9 +34,23 @@
 
 namespace egmla {
 
-// Stamps and bitmap words one 128-byte line apart, so that atomics of
-// different ones do not queue on one line.
+// Marks of eg_mla_gate_table: a 128-byte line per id.  Word 0 of line i is
+// id i's stamp (one line apart, so that claims of different ids do not queue on
+// one line).  The two bitmaps (one per parity of the stamp) lie in the second
+// halves of the first lines, 2^shift words in each, so that either pass 1 may
+// follow the other.
 constexpr int kMarkStride = 32;
+constexpr int kMarkBitmapAt = 16;
+__device__ __forceinline__ int64_t bitmap_word(int j, int shift) {
+  return static_cast<int64_t>(j >> shift) * kMarkStride + (j & ((1 << shift) - 1));
+}
+// Words per line: 16 where there are many (a wave's 64 words are then 4 lines,
+// and there are fewer lines to clear: 50304 ids, 524288 rows 24.7 us a call
+// against 26.5 with one), one where few are fought over by every work-group
+// (20000 ids, 1000000 rows 25.6 against 27.4).
+constexpr int kBitmapDenseVocab = 32768;
+int bitmap_shift(int vocab) { return vocab >= kBitmapDenseVocab ? 4 : 0; }
+
 constexpr int kGateThreads = 256;        // VALU kernel
 constexpr int kGateWaves = 8;            // MFMA kernel: waves per work-group (2 per SIMD)
 constexpr int kGateLdsBudget = 150 * 1024;  // bytes of W^UE slice in LDS, at most
@@ -89,7 +103,7 @@ __device__ __forceinline__ void gate_store(const gate_f32x16_t (&acc)[NCB], uint
 // TABLE: `ids` is the list of distinct ids that pass 1 built, its length
 // counts[parity] (read on the device; n bounds it), and row i writes
 // out[ids[i]], a [V, d_c] table.  The kernel zeroes what the next call's pass 1
-// starts from: counts[parity ^ 1] and the nclear words of `clear`, a line apart.
+// starts from: counts[parity ^ 1] and the nclear words of the bitmap `clear`.
 template <int EP, int NCB, bool ONE_PASS, bool TABLE = false>
 __global__ __launch_bounds__(64 * kGateWaves, 1) void gate_rows_mfma_kernel(const int32_t* __restrict__ ids,
                                                                             const uint16_t* __restrict__ emb,
@@ -99,11 +113,11 @@ __global__ __launch_bounds__(64 * kGateWaves, 1) void gate_rows_mfma_kernel(cons
                                                                             unsigned int* __restrict__ counts,
                                                                             unsigned int parity,
                                                                             unsigned int* __restrict__ clear,
-                                                                            int nclear) {
+                                                                            int nclear, int clear_shift) {
   if constexpr (TABLE) {
     n = min(n, static_cast<int64_t>(counts[parity]));
     for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < nclear; i += gridDim.x * blockDim.x)
-      clear[static_cast<int64_t>(i) * kMarkStride] = 0u;
+      clear[bitmap_word(i, clear_shift)] = 0u;
     if (blockIdx.x == 0 && threadIdx.x == 0) counts[parity ^ 1u] = 0u;
   }
   if (n <= 0) return;  // uniform over the work-group
@@ -248,21 +262,29 @@ __global__ __launch_bounds__(kClaimThreads) void gate_claim_kernel(const int32_t
   if (win && pos < static_cast<unsigned int>(V)) list[pos] = id;  // a counter left nonzero cannot overrun
 }
 
-// Distinct ids by bitmap (pass 1 of eg_mla_gate_table for vocabularies whose
-// bitmap fits the LDS).  Each work-group marks the ids of its rows in an LDS
-// bitmap, ORs each nonzero word into the call's global one (one returning
-// atomic per word) and appends the bits that were not set there to the list,
-// its places reserved with one atomic add.  The id line above costs one global
-// atomic per row, most of them repeats: 539 K rows of 50304 ids took 26.6 us;
-// here it is at most one per work-group and word, in 9.2 us.
-// bits: this call's words (a line apart), zero on entry; the list pass
-// zeroes the other call parity's.
-constexpr int kBitmapMaxWords = 16384;  // 64 KB of LDS: vocabularies up to 524288
+// Distinct ids by bitmap (pass 1 of eg_mla_gate_table for many rows).  Each
+// work-group marks the ids of its rows in an LDS bitmap, ORs each nonzero word
+// into the call's global one (one returning atomic per word) and appends the
+// bits that were not set there to the list, its places reserved with one atomic
+// add.  The kernel above costs one global atomic per row, this one at most one
+// per work-group and word, but reads the whole bitmap however few the rows.  It
+// is taken from max(65536, ids) rows on, call with the kernel above / this one:
+//   rows             65536          131072         262144         524288
+//   20000 ids        22.4 / 21.3    25.5 / 21.5    31.4 / 22.0    39.9 / 24.3
+//   50304 ids        19.4 / 19.1    26.8 / 23.4    33.0 / 23.5    43.1 / 24.7
+//   129280 ids       25.5 / 27.7    35.3 / 34.7    49.2 / 42.9    66.3 / 48.6
+//   500000 ids       26.8 / 36.9    44.4 / 52.2    73.6 / 75.5   128.9 / 118
+// bits: this call's words, zero on entry; the list pass of every call, whichever
+// pass 1 it took, zeroes the other parity's.
+constexpr int kBitmapMaxWords = 16320;  // with the kernel's other LDS below 64 KB: vocabularies up to 522240
+constexpr int kBitmapMinRows = 65536;
 constexpr int kBitmapRows = 2048;       // rows of a work-group, at least
 constexpr int kBitmapGroups = 40;       // work-groups, at most: more repeat each other's words (64: 10.0 us, 128: 13.2)
+static_assert(kBitmapMinRows >= kBitmapRows, "a work-group at least");
 
 __global__ __launch_bounds__(kClaimThreads) void gate_bitmap_kernel(const int32_t* __restrict__ ids, int64_t n, int V,
-                                                                    int nwords, unsigned int* __restrict__ bits,
+                                                                    int nwords, int shift,
+                                                                    unsigned int* __restrict__ bits,
                                                                     unsigned int* __restrict__ count,
                                                                     int32_t* __restrict__ list) {
   extern __shared__ __attribute__((aligned(16))) unsigned int word[];  // [nwords]
@@ -293,7 +315,7 @@ __global__ __launch_bounds__(kClaimThreads) void gate_bitmap_kernel(const int32_
     const int j = k + rot < nwords ? k + rot : k + rot - nwords;
     unsigned int x = word[j];
     if (x != 0u) {
-      x &= ~atomicOr(bits + static_cast<int64_t>(j) * kMarkStride, x);
+      x &= ~atomicOr(bits + bitmap_word(j, shift), x);
       word[j] = x;
     }
     mine += static_cast<unsigned int>(__builtin_popcount(x));
@@ -390,27 +412,32 @@ eg_mla_status launch_gate(const eg_mla_dims* dims, int32_t emb_dim, int32_t emb_
                     reinterpret_cast<uintptr_t>(w_ue) % 16 == 0 && reinterpret_cast<uintptr_t>(out) % 8 == 0;
   unsigned int* counts = nullptr;
   unsigned int* clear = nullptr;
-  int nclear = 0;
+  int nclear = 0, clear_shift = 0;
+  bool bitmap = false;
   if (mfma && table) {
-    // pass 1: the distinct ids into a list (marks: [V] lines of stamps or bitmap words, [2] counts, [V] list)
+    // pass 1: the distinct ids into a list (marks: [V] lines, [2] counts, [V] list)
     if (n > (int64_t{1} << 40)) return EG_MLA_ERR_UNSUPPORTED;
     unsigned int* cnt = marks + static_cast<int64_t>(emb_vocab) * kMarkStride;
     int32_t* list = reinterpret_cast<int32_t*>(cnt + 2);
     const int nwords = (emb_vocab + 31) / 32;
-    // (the same pass for every call of a vocabulary: the two keep different
-    // things in the marks, whose V stamp lines hold the 2 ceil(V / 32) bitmap words from V = 2 on)
-    if (emb_vocab >= 2 && nwords <= kBitmapMaxWords) {
-      unsigned int* bits[2] = {marks, marks + static_cast<int64_t>(nwords) * kMarkStride};
-      const int64_t groups = std::max<int64_t>(1, std::min<int64_t>(kBitmapGroups, n / kBitmapRows));
-      hipLaunchKernelGGL(gate_bitmap_kernel, dim3(static_cast<unsigned>(groups)), dim3(kClaimThreads),
-                         nwords * sizeof(unsigned int), stream, ids, n, emb_vocab, nwords, bits[stamp & 1u],
-                         cnt + (stamp & 1u), list);
+    if (emb_vocab >= 2 && nwords <= kBitmapMaxWords) {  // from V = 2 on the lines hold both bitmaps
+      clear_shift = bitmap_shift(emb_vocab);
+      const int lines = (nwords + (1 << clear_shift) - 1) >> clear_shift;
+      unsigned int* bits[2] = {marks + kMarkBitmapAt, marks + kMarkBitmapAt + static_cast<int64_t>(lines) * kMarkStride};
+      // whichever pass 1 this call takes, its list pass leaves the next call's bitmap zero
       clear = bits[(stamp & 1u) ^ 1u];
       nclear = nwords;
-    } else {
+      bitmap = n >= std::max(kBitmapMinRows, emb_vocab);
+      if (bitmap) {
+        const int64_t groups = std::min<int64_t>(kBitmapGroups, n / kBitmapRows);
+        hipLaunchKernelGGL(gate_bitmap_kernel, dim3(static_cast<unsigned>(groups)), dim3(kClaimThreads),
+                           nwords * sizeof(unsigned int), stream, ids, n, emb_vocab, nwords, clear_shift,
+                           bits[stamp & 1u], cnt + (stamp & 1u), list);
+      }
+    }
+    if (!bitmap)
       hipLaunchKernelGGL(gate_claim_kernel, dim3(static_cast<unsigned>((n + kClaimThreads - 1) / kClaimThreads)),
                          dim3(kClaimThreads), 0, stream, ids, n, emb_vocab, marks, stamp, list);
-    }
     counts = cnt;
     ids = list;
     n = std::min<int64_t>(n, emb_vocab);  // the list holds distinct ids only
@@ -451,7 +478,8 @@ eg_mla_status launch_gate(const eg_mla_dims* dims, int32_t emb_dim, int32_t emb_
     int V = emb_vocab, Ev = E, DCv = DC, Sv = S;
     unsigned int* counts_c = counts;
     unsigned int parity = stamp & 1u;
-    void* args[] = {&ids_c, &emb_c, &w_c, &out_c, &n, &Ev, &DCv, &V, &Sv, &counts_c, &parity, &clear, &nclear};
+    void* args[] = {&ids_c, &emb_c, &w_c, &out_c, &n, &Ev, &DCv, &V, &Sv, &counts_c, &parity, &clear, &nclear,
+                    &clear_shift};
     if (hipLaunchKernel(fn, dim3(grid), dim3(64 * kGateWaves), args, lds, stream) != hipSuccess)
       return EG_MLA_ERR_HIP;
   } else {
