@@ -173,7 +173,10 @@ eg_mla_status eg_mla_append_ws(const eg_mla_dims* dims, int32_t n_tokens, int32_
  *                 b * max_pages_per_seq * P + j
  *   workspace     device scratch of at least
  *                 eg_mla_decode_workspace_size(dims, B, max_pages_per_seq, plan)
- *                 bytes, 256-byte aligned; contents need no initialisation
+ *                 bytes, 256-byte aligned; contents need no initialisation.
+ *                 (A smaller batch or context may ask for more: a workspace
+ *                 kept for several sizes has the largest of their sizes.  Some
+ *                 calls do with less than the query says, with longer splits.)
  *   out           [B, H, d_v]  in the storage type
  *
  * Arithmetic (bf16 storage, MFMA path): each gated latent is the exact fp32
@@ -211,9 +214,9 @@ eg_mla_status eg_mla_decode_planned(const eg_mla_dims* dims, int32_t batch, cons
  * eg_mla_decode, minus the workspace: the call uses a scratch array of
  * EG_MLA_NOALLOC_SCRATCH_BYTES bytes that the library holds in device memory
  * (one per GPU, for as long as the process runs) and allocates nothing.
- *   - A call whose plan needs more than EG_MLA_NOALLOC_SCRATCH_BYTES of
- *     workspace (eg_mla_decode_workspace_size with a NULL plan) returns
- *     EG_MLA_ERR_WORKSPACE before anything is enqueued; so do the checks of
+ *   - A call that cannot do with EG_MLA_NOALLOC_SCRATCH_BYTES of workspace
+ *     (any call whose eg_mla_decode_workspace_size with a NULL plan is no
+ *     larger can) returns EG_MLA_ERR_WORKSPACE before anything is enqueued; so do the checks of
  *     eg_mla_decode (status codes as there).  32 MiB covers batch 32 at
  *     context 4096, batch 4 at 32768 and batch 256 at 2048 of the 16-head
  *     d_c = 128 layer, not the 128-head d_c = 512 one.

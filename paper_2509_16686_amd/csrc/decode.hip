@@ -799,9 +799,8 @@ extern "C" eg_mla_status eg_mla_decode_noalloc(const eg_mla_dims* dims, int32_t 
   eg_mla_status st = check_dims(dims);
   if (st != EG_MLA_OK) return st;
   if (batch < 0 || max_pages_per_seq < 0) return EG_MLA_ERR_INVALID_ARG;
-  st = make_decode_plan(*dims, batch, max_pages_per_seq, nullptr, &p);
+  st = fit_decode_plan(*dims, batch, max_pages_per_seq, nullptr, EG_MLA_NOALLOC_SCRATCH_BYTES, &p);
   if (st != EG_MLA_OK) return st;
-  if (p.bytes > EG_MLA_NOALLOC_SCRATCH_BYTES) return EG_MLA_ERR_WORKSPACE;
   if (batch == 0) return validate_decode(dims, batch, q, latent_cache, token_id_cache, gate_table, w_uk, w_uv,
                                          seq_lens, max_pages_per_seq, num_slots, page_table, nullptr, 0, out,
                                          nullptr, &p);

@@ -79,7 +79,7 @@ eg_mla_status check_dims(const eg_mla_dims* d) {
 }
 
 eg_mla_status make_decode_plan(const eg_mla_dims& d, int32_t batch, int32_t max_pages_per_seq,
-                               const eg_mla_plan* plan, DecodePlan* out) {
+                               const eg_mla_plan* plan, DecodePlan* out, PlanRows rows_rule) {
   DecodePlan p;
   const int forced = plan ? plan->path : EG_MLA_PATH_AUTO;
   if (forced != EG_MLA_PATH_AUTO && forced != EG_MLA_PATH_VALU && forced != EG_MLA_PATH_MFMA)
@@ -94,8 +94,8 @@ eg_mla_status make_decode_plan(const eg_mla_dims& d, int32_t batch, int32_t max_
 
   // The vector kernel stays for the shapes the fp32 matrix-core kernel does
   // not take, for explicit splits past its token list, and when asked for.
-  p.f32_mfma = p.path == EG_MLA_PATH_VALU && forced == EG_MLA_PATH_AUTO && f32_kernel_shape(d) &&
-               (plan == nullptr || plan->split_tokens <= kMaxSplitTokens);
+  p.f32_mfma = rows_rule != PlanRows::kMost && p.path == EG_MLA_PATH_VALU && forced == EG_MLA_PATH_AUTO &&
+               f32_kernel_shape(d) && (plan == nullptr || plan->split_tokens <= kMaxSplitTokens);
   if (p.path == EG_MLA_PATH_MFMA) {
     p.heads_per_group = heads_kernel_shape(d) ? kHeadsPerItemWide : 16;
   } else if (p.f32_mfma) {
@@ -114,7 +114,7 @@ eg_mla_status make_decode_plan(const eg_mla_dims& d, int32_t batch, int32_t max_
   p.slices = sliced_kernel && req_slices == kIdSlices ? kIdSlices : 1;
   const bool rows_kernel = p.path == EG_MLA_PATH_MFMA && rows_kernel_shape(d);
   // kernels whose waves own whole units of tokens take short splits
-  const bool unit_kernel = (sliced_kernel && p.slices == 1) || rows_kernel;
+  const bool unit_kernel = rows_rule == PlanRows::kFast && ((sliced_kernel && p.slices == 1) || rows_kernel);
   const int max_split = sliced_kernel ? kMaxSliceSplitTokens : kMaxSplitTokens;
 
   int split = plan ? plan->split_tokens : 0;
@@ -129,7 +129,7 @@ eg_mla_status make_decode_plan(const eg_mla_dims& d, int32_t batch, int32_t max_
         p.path == EG_MLA_PATH_MFMA && (tok_kernel_shape(d) || heads_kernel_shape(d)) ? kTargetWorkItemsTok
         // (measured: 256 x 2048 117 us per call against 122 with two work-groups
         // per compute unit, 32 x 4096 42.5 against 47.9)
-        : rows_kernel ? kTargetWorkItemsTok
+        : rows_kernel && rows_rule != PlanRows::kMost ? kTargetWorkItemsTok
         : p.f32_mfma ? (d.latent_dim <= 64 ? kTargetWorkItemsF32 : kTargetWorkItemsF32 / 2)
                      : kTargetWorkItems;
     int64_t s = (work + target - 1) / target;
@@ -206,7 +206,7 @@ eg_mla_status make_decode_plan(const eg_mla_dims& d, int32_t batch, int32_t max_
   // itself evens out the work-groups, nor where the search's largest piece (about
   // N / (pieces - batch), see tok_sizes) could outgrow the token list, nor where the extra partial rows would take a call that fits
   // the workspace-free entry's scratch out of it.
-  if (sliced_kernel && p.slices == 1 && !p.fused_absorb && d.head_dim == 128 && batch > 32 && p.s_max < 8 &&
+  if (rows_rule == PlanRows::kFast && sliced_kernel && p.slices == 1 && !p.fused_absorb && d.head_dim == 128 && batch > 32 && p.s_max < 8 &&
       (plan == nullptr || plan->split_tokens == 0) && p.capacity >= kTokBalancedMinCap &&
       p.split_tokens >= (nblk > kTargetWorkItemsTok ? kTokBalancedUneven : kTokBalancedEven) &&
       batch <= kTokMaxBatch) {
@@ -229,6 +229,24 @@ eg_mla_status make_decode_plan(const eg_mla_dims& d, int32_t batch, int32_t max_
   return EG_MLA_OK;
 }
 
+eg_mla_status fit_decode_plan(const eg_mla_dims& d, int32_t batch, int32_t max_pages_per_seq, const eg_mla_plan* plan,
+                              size_t workspace_bytes, DecodePlan* out) {
+  eg_mla_status st = make_decode_plan(d, batch, max_pages_per_seq, plan, out);
+  if (st != EG_MLA_OK || out->bytes <= workspace_bytes) return st;
+  st = make_decode_plan(d, batch, max_pages_per_seq, plan, out, PlanRows::kFew);
+  return st != EG_MLA_OK || out->bytes <= workspace_bytes ? st : EG_MLA_ERR_WORKSPACE;
+}
+
+size_t decode_workspace_bytes(const eg_mla_dims& d, int32_t batch, int32_t max_pages_per_seq, const eg_mla_plan* plan) {
+  size_t bytes = 0;
+  for (const PlanRows rows : {PlanRows::kFast, PlanRows::kFew, PlanRows::kMost}) {
+    DecodePlan p;
+    if (make_decode_plan(d, batch, max_pages_per_seq, plan, &p, rows) != EG_MLA_OK) return 0;
+    bytes = std::max(bytes, p.bytes);
+  }
+  return bytes;
+}
+
 eg_mla_status validate_decode(const eg_mla_dims* d, int32_t batch, const void* q, const void* latent_cache,
                               const int32_t* token_id_cache, const void* gate_table, const void* w_uk,
                               const void* w_uv, const int32_t* seq_lens, int32_t max_pages_per_seq,
@@ -238,8 +256,8 @@ eg_mla_status validate_decode(const eg_mla_dims* d, int32_t batch, const void* q
   if (st != EG_MLA_OK) return st;
   if (batch < 0 || max_pages_per_seq < 0 || num_slots < 0) return EG_MLA_ERR_INVALID_ARG;
   if (num_slots >= (int64_t{1} << 31)) return EG_MLA_ERR_UNSUPPORTED;  // 32-bit row indices in the kernels
-  st = make_decode_plan(*d, batch, max_pages_per_seq, plan, p);
-  if (st != EG_MLA_OK) return st;
+  const eg_mla_status fit = fit_decode_plan(*d, batch, max_pages_per_seq, plan, workspace_bytes, p);
+  if (fit != EG_MLA_OK && fit != EG_MLA_ERR_WORKSPACE) return fit;
   if (batch == 0) return EG_MLA_OK;
   if (!q || !gate_table || !w_uk || !w_uv || !seq_lens || !out) return EG_MLA_ERR_INVALID_ARG;
   if (max_pages_per_seq > 0 && (!latent_cache || !token_id_cache)) return EG_MLA_ERR_INVALID_ARG;
@@ -253,7 +271,7 @@ eg_mla_status validate_decode(const eg_mla_dims* d, int32_t batch, const void* q
   // 16-byte vector loads of rows and weights
   if (!aligned16(q) || !aligned16(latent_cache) || !aligned16(gate_table) || !aligned16(w_uk) || !aligned16(w_uv))
     return EG_MLA_ERR_INVALID_ARG;
-  if (!workspace || workspace_bytes < p->bytes) return EG_MLA_ERR_WORKSPACE;
+  if (!workspace || fit != EG_MLA_OK) return EG_MLA_ERR_WORKSPACE;
   if (reinterpret_cast<uintptr_t>(workspace) % kAlign != 0) return EG_MLA_ERR_WORKSPACE;
   return EG_MLA_OK;
 }
@@ -450,9 +468,7 @@ eg_mla_status eg_mla_check_dims(const eg_mla_dims* dims) { return egmla::check_d
 size_t eg_mla_decode_workspace_size(const eg_mla_dims* dims, int32_t batch, int32_t max_pages_per_seq,
                                     const eg_mla_plan* plan) {
   if (egmla::check_dims(dims) != EG_MLA_OK || batch < 0 || max_pages_per_seq < 0) return 0;
-  egmla::DecodePlan p;
-  if (egmla::make_decode_plan(*dims, batch, max_pages_per_seq, plan, &p) != EG_MLA_OK) return 0;
-  return p.bytes;
+  return egmla::decode_workspace_bytes(*dims, batch, max_pages_per_seq, plan);
 }
 
 size_t eg_mla_prefill_workspace_size(const eg_mla_dims* dims, int32_t seq_len) {

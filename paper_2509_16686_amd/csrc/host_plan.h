@@ -73,12 +73,25 @@ struct DecodePlan {
   size_t bytes = 0;     // rows: B * s_max * slices, or kWideMaxGroups + B, or `pieces`, when balanced
 };
 
+// Which automatic plan: the fastest; the one with the fewest partial rows, for a
+// workspace that does not hold the first (no balanced pieces, no split below
+// 256 tokens); and, for the size query only, the one with the most rows that a
+// call of the shape may bring (the vector kernel's splits, short d_c 320 ones),
+// so that a workspace sized at a server's largest batch serves smaller ones too.
+enum class PlanRows { kFast, kFew, kMost };
+
 eg_mla_status check_dims(const eg_mla_dims* d);
 
 // Resolves `plan` (NULL = automatic) for a decode call.  Returns
 // EG_MLA_ERR_UNSUPPORTED when a forced path is unavailable for the shape.
 eg_mla_status make_decode_plan(const eg_mla_dims& d, int32_t batch, int32_t max_pages_per_seq,
-                               const eg_mla_plan* plan, DecodePlan* out);
+                               const eg_mla_plan* plan, DecodePlan* out,
+                               PlanRows rows = PlanRows::kFast);
+// The plan for a call with `workspace_bytes` of workspace (EG_MLA_ERR_WORKSPACE if
+// neither the fast plan nor the one with few rows fits), and the size to ask for.
+eg_mla_status fit_decode_plan(const eg_mla_dims& d, int32_t batch, int32_t max_pages_per_seq, const eg_mla_plan* plan,
+                              size_t workspace_bytes, DecodePlan* out);
+size_t decode_workspace_bytes(const eg_mla_dims& d, int32_t batch, int32_t max_pages_per_seq, const eg_mla_plan* plan);
 
 // Checks every host-visible argument of a decode call (pointers, sizes,
 // workspace) against the resolved plan.

@@ -27,7 +27,7 @@ def gpu():
 
 @pytest.fixture(scope="session")
 def tok_pieces(tmp_path_factory):
-    """Runs the host build of the d_c 128 decode's plan and balanced schedule (tok_pieces_host.cpp)."""
+    """Runs the host build of the decode plan and the d_c 128 decode's balanced schedule (tok_pieces_host.cpp)."""
     cxx = shutil.which("g++") or shutil.which("c++")
     assert cxx, "no C++ compiler"
     exe = str(tmp_path_factory.mktemp("tok_pieces") / "tok_pieces_host")

@@ -120,6 +120,26 @@ def test_short_splits(gpu, lens):
     assert_close(decode(inp), oracle_decode(inp), "bf16", f"short splits {lens}")
 
 
+@pytest.mark.gpu
+@pytest.mark.parametrize("wl,most,batch,top", [
+    (W.WORKLOADS[1], 256, 100, 4096),           # balanced pieces do not fit the workspace of 256 sequences
+    (W.WORKLOADS[1], 64, 40, 4096),
+    (W.MLA_DC320_BIGBATCH, 64, 50, 1024),       # whole-row kernel
+])
+def test_workspace_of_a_larger_batch(gpu, wl, most, batch, top):
+    wl = wl.replace(batch=batch, vocab=900, seq_len=None, seq_len_range=(0, top), page_size=64, paged=True, seed=12)
+    lens = np.random.default_rng(3).integers(0, top + 1, batch).astype(np.int32)
+    dd = B.stage_decode(W.generate(wl, seq_lens=lens))
+    import torch
+    say(f"decode d_c {wl.latent_dim} B={batch} in the workspace of B={most}")
+    want = B.run_decode(dd).double()
+    dd.out = torch.full_like(dd.out, float("nan"))
+    got = B.run_decode(dd, workspace=B.alloc_workspace(B.decode_workspace_size(dd.dims, most, top // 64))).double()
+    torch.cuda.synchronize()
+    # two bf16 outputs of sums in another order
+    assert torch.isfinite(got).all() and (got - want).norm() <= 5e-3 * want.norm()
+
+
 def test_balanced_workspace_fits_the_scratch_as_before():
     """A batch whose (sequence, split) plan fits the 32 MiB scratch fits it with the plan it gets."""
     d = B.make_dims(num_heads=16, head_dim=128, v_head_dim=128, latent_dim=128, rope_dim=64, vocab_size=50304)

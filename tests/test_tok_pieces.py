@@ -1,4 +1,4 @@
-"""Pieces of the d_c 128 decode's balanced schedule, cut on the host by the device's own arithmetic."""
+"""Pieces of the d_c 128 decode's balanced schedule, cut on the host by the device's own arithmetic, and workspaces."""
 import pytest
 
 TOKEN_LIST = 4096  # tokens a work-group of the split kernel can list
@@ -21,3 +21,15 @@ def test_long_batches(tok_pieces, batch, length):
     cut = tok_pieces("cut", 16, batch, length, text=f"{length} " * batch)
     assert len(cut) <= pieces and max(t for _, _, t in cut) <= TOKEN_LIST
     assert sum(t for _, _, t in cut) == batch * length
+
+
+@pytest.mark.parametrize("layer", [(16, 128, 128, 128, 64, 1), (32, 128, 128, 128, 64, 1), (16, 128, 128, 320, 64, 1),
+                                   (12, 64, 64, 64, 64, 1), (12, 64, 64, 256, 64, 1), (4, 32, 32, 32, 0, 0),
+                                   (128, 128, 128, 512, 64, 1)], ids=str)
+def test_a_workspace_serves_smaller_batches(tok_pieces, layer):
+    """A workspace sized once, at a server's largest batch, holds every smaller batch whose plan of whole splits of 256
+    tokens (or the vector kernel's) it holds: balanced pieces and short splits give way where they do not fit."""
+    for batch in (8, 64, 128, 256, 384, 512):
+        for cap in (512, 1024, 2048, 4096, 32768):
+            whole, held, _ = tok_pieces("server", *layer, batch, cap)[0]
+            assert whole > 0 and held == whole, (batch, cap)

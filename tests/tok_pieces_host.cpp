@@ -1,12 +1,15 @@
-// Host run of the d_c 128 decode's balanced schedule: the plan from
-// host_plan.cpp and the pieces from tok_pieces.h, step by step as tok_schedule
-// takes them on the device.
+// Host run of the decode plan (host_plan.cpp) and of the d_c 128 decode's
+// balanced schedule (tok_pieces.h, step by step as tok_schedule takes it on the
+// device).
 //
 //   plan H B CAP          prints the plan: balanced (0 or 1), pieces, split, workspace bytes
 //   cut H B CAP           reads B lengths from stdin; prints "sequence first tokens" per piece
 //   sweep H               every batch with a balanced schedule, lengths to the capacity, equal and
 //                         mixed; prints "balanced plans, cuts, longest piece" and fails on a piece
 //                         beyond the token list, too many pieces or tokens not covered once
+//   server H DH DV DC DR DTYPE B CAP
+//                         batches up to B that one workspace, sized for B, holds and that plans
+//                         with the most rows fit: "batches fitting of them, all fitting"
 #include <algorithm>
 #include <cstdio>
 #include <cstdlib>
@@ -116,9 +119,33 @@ int sweep(int heads) {
   return 0;
 }
 
+int server(char** v) {
+  eg_mla_dims d = layer(std::atoi(v[0]));
+  d.head_dim = std::atoi(v[1]);
+  d.v_head_dim = std::atoi(v[2]);
+  d.latent_dim = d.gate_dim = std::atoi(v[3]);
+  d.rope_dim = std::atoi(v[4]);
+  d.dtype = std::atoi(v[5]);
+  const int B = std::atoi(v[6]), cap = std::atoi(v[7]);
+  const size_t bytes = decode_workspace_bytes(d, B, cap, nullptr);
+  int old_fit = 0, both = 0, now = 0;
+  for (int b = 1; b <= B; ++b) {
+    DecodePlan p;
+    if (make_decode_plan(d, b, cap, nullptr, &p, PlanRows::kMost) != EG_MLA_OK) return 2;
+    const bool most = p.bytes <= bytes, fit = fit_decode_plan(d, b, cap, nullptr, bytes, &p) == EG_MLA_OK;
+    if (fit && p.bytes > bytes) return 2;
+    old_fit += most;
+    both += most && fit;
+    now += fit;
+  }
+  std::printf("%d %d %d\n", old_fit, both, now);
+  return 0;
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
+  if (argc == 10 && !std::strcmp(argv[1], "server")) return server(argv + 2);
   if (argc == 3 && !std::strcmp(argv[1], "sweep")) return sweep(std::atoi(argv[2]));
   if (argc != 5) return 2;
   const int heads = std::atoi(argv[2]), B = std::atoi(argv[3]), cap = std::atoi(argv[4]);
