@@ -546,7 +546,7 @@ __global__ __launch_bounds__(kCombWideWaves * 64) void combine_wide_kernel(const
 // ---------------------------------------------------------------------------
 constexpr int kComb4Seq = 4;
 
-template <int DC, int DV>
+template <int DC, int DV, bool ROWS>
 __device__ __forceinline__ void combine4_block(const float* __restrict__ part_ml, const float* __restrict__ part_o,
                                                const uint16_t* __restrict__ w_uv,
                                                const int32_t* __restrict__ seq_lens, uint16_t* __restrict__ out,
@@ -578,7 +578,7 @@ __device__ __forceinline__ void combine4_block(const float* __restrict__ part_ml
     int ns = 0;
     int64_t row0 = static_cast<int64_t>(b) * s_max * slices;
     if (w < nseq) {
-      if (seq_rows) {
+      if constexpr (ROWS) {
         const int2 sr = seq_rows[b];
         row0 = sr.x;
         ns = sr.y;
@@ -639,14 +639,15 @@ __device__ __forceinline__ void combine4_block(const float* __restrict__ part_ml
     }
   }
 }
-template <int DC, int DV>
+// ROWS: the partials are the rows that seq_rows lists (balanced schedule)
+template <int DC, int DV, bool ROWS>
 __global__ __launch_bounds__(256) void combine4_kernel(const float* __restrict__ part_ml, const float* __restrict__ part_o,
                                                        const uint16_t* __restrict__ w_uv, const int32_t* __restrict__ seq_lens,
                                                        uint16_t* __restrict__ out, int B, int H, int cap, int split,
                                                        int s_max, int slices, const int2* __restrict__ seq_rows,
                                                        Stamps stamps) {
   __shared__ __attribute__((aligned(16))) uint16_t o_s[2 * kComb4Seq * (DC + 8)];
-  combine4_block<DC, DV>(part_ml, part_o, w_uv, seq_lens, out, B, H, cap, split, s_max, slices, seq_rows, blockIdx.x,
+  combine4_block<DC, DV, ROWS>(part_ml, part_o, w_uv, seq_lens, out, B, H, cap, split, s_max, slices, seq_rows, blockIdx.x,
                          blockIdx.y * kComb4Seq, o_s, stamps);
 }
 

@@ -365,8 +365,10 @@ hipError_t launch_combine_dc(dim3 grid, hipStream_t stream, const float* pm, con
   // (64 sequences of 2048: 4.0 against 5.5 us).
   const int64_t small_wg = static_cast<int64_t>(H) * ((B + kComb4Seq - 1) / kComb4Seq);
   if ((seq_rows ? DC == 128 : static_cast<int64_t>(s_max) * slices <= 8) && small_wg <= 512) {
-    hipLaunchKernelGGL((combine4_kernel<DC, 128>), dim3(H, (B + kComb4Seq - 1) / kComb4Seq), dim3(256), 0, stream,
-                       pm, po, wv, seq_lens, ov, B, H, cap, split, s_max, slices, seq_rows, stamps);
+    auto kern = combine4_kernel<DC, 128, false>;
+    if constexpr (DC == 128) kern = seq_rows ? combine4_kernel<DC, 128, true> : kern;
+    hipLaunchKernelGGL(kern, dim3(H, (B + kComb4Seq - 1) / kComb4Seq), dim3(256), 0, stream, pm, po, wv, seq_lens, ov,
+                       B, H, cap, split, s_max, slices, seq_rows, stamps);
     return hipGetLastError();
   }
   const size_t lds = combine_lds_bytes(DC);
