@@ -17,6 +17,7 @@ constexpr int kTargetWorkItemsTok = 256;
 // 64-token splits, 16.9 with 256), while the partials of a sequence stay few
 // (1 x 32768: 18.7 us with 128 partials, 19.8 with 256).
 constexpr int kMaxPartialsTok = 128;
+constexpr int kMergeValueDim = 128;  // value dim of the MFMA merge kernels (run_decode)
 constexpr int kMinSplitTok = 64;
 // The d_c 128 kernel takes the balanced schedule from this capacity on, where a
 // (sequence, split) item is long enough to pay for the schedule (about 2 us):
@@ -140,12 +141,31 @@ eg_mla_status make_decode_plan(const eg_mla_dims& d, int32_t batch, int32_t max_
                                                                      : 128;
     s = std::max<int64_t>(s, min_split);
     if (unit_kernel) s = std::max<int64_t>(s, (p.capacity / kMaxPartialsTok + kTile - 1) / kTile * kTile);
-    // short splits only where the items still run one per compute unit (48 x
-    // 1000: 288 items of 192 tokens 18.8 us per call, 192 of 256 17.1)
-    if (sliced_kernel && unit_kernel && s < 256 &&
-        static_cast<int64_t>(std::max(batch, 1)) * p.head_groups * ceil_div(std::max(p.capacity, 1), static_cast<int>(s)) >
-            kTargetWorkItemsTok)
-      s = 256;
+    // the general merge reads a sequence's partials one after the other: no more
+    // than 16 for the sake of short splits (d_v 64, 1 x 4096: 64 partials 21.6 us
+    // per call, 16 18.4; 1 x 2048: 32 18.0, 16 17.0)
+    if (unit_kernel && d.v_head_dim != kMergeValueDim && s < 256)
+      s = std::max<int64_t>(s, std::min(256, ceil_div(p.capacity, 16 * kTile) * kTile));
+    if (sliced_kernel && unit_kernel && s < 256) {
+      const int64_t per_split = static_cast<int64_t>(std::max(batch, 1)) * p.head_groups;
+      const int cap = std::max(p.capacity, 1);
+      auto cut = [&](int n) { return std::max(kMinSplitTok, ceil_div(cap, n * kTile) * kTile); };
+      // Short splits only where the items still run one per compute unit (48 x
+      // 1000: 288 items of 192 tokens 18.8 us per call, 192 of 256 17.1), and
+      // 16 or 8 a sequence rather than some number between: the absorption is
+      // then shared evenly, and 8 partials merge in small work-groups.  With up
+      // to 16 sequences the splits above come to at most 16.  With more, 8 up
+      // to 192 tokens (us per call: as above / 8 splits / of 256 tokens):
+      //   20 x 1300  17.6 / 16.1 / 17.2    24 x 1500  18.3 / 16.6 / 17.3
+      //   28 x 1100  18.0 / 16.5 / 17.3    20 x 900   16.6 / 15.9 / 17.0
+      // and 256 tokens from there to 2048 (24 x 1600 18.2 / 17.7 / 17.3, 28 x
+      // 1800 19.9 / 18.6 / 18.7); above, more than 8 splits are due anyway
+      // (20 x 2300 18.1 / 18.7 / 19.1).
+      if (per_split > 16 && 8 * per_split <= kTargetWorkItemsTok && cap <= 8 * 256)
+        s = cut(8) <= 192 ? cut(8) : 256;
+      else if (per_split * ceil_div(cap, static_cast<int>(s)) > kTargetWorkItemsTok)
+        s = per_split <= 16 && cut(16) < 256 ? cut(16) : 256;  // (12 x 2048: 264 items; 16 splits 15.5, of 256 tokens 17.5)
+    }
     s = std::min<int64_t>(s, max_split);
     split = static_cast<int>(s);
   }

@@ -23,6 +23,18 @@ def test_long_batches(tok_pieces, batch, length):
     assert sum(t for _, _, t in cut) == batch * length
 
 
+@pytest.mark.parametrize("batch,cap,v_dim,split", [
+    (1, 64, 128, 64), (16, 1024, 128, 64), (1, 32768, 128, 256),   # one unit per wave, at most 128 partials
+    (12, 2048, 128, 128), (14, 2048, 128, 128),                    # 16 splits a sequence where 64 to 96 tokens are too many items
+    (20, 600, 128, 96), (24, 1500, 128, 192), (32, 1100, 128, 160),  # 8 splits
+    (20, 1600, 128, 256), (28, 2048, 128, 256), (48, 1000, 128, 256),
+    (1, 1024, 64, 64), (4, 2048, 64, 128), (1, 4096, 64, 256), (1, 32768, 64, 256),  # the general merge: few partials
+])
+def test_automatic_splits(tok_pieces, batch, cap, v_dim, split):
+    balanced, _, got, _ = tok_pieces("plan", 16, batch, cap, v_dim)[0]
+    assert not balanced and got == split
+
+
 @pytest.mark.parametrize("layer", [(16, 128, 128, 128, 64, 1), (32, 128, 128, 128, 64, 1), (16, 128, 128, 320, 64, 1),
                                    (12, 64, 64, 64, 64, 1), (12, 64, 64, 256, 64, 1), (4, 32, 32, 32, 0, 0),
                                    (128, 128, 128, 512, 64, 1)], ids=str)

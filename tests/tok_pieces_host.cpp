@@ -2,7 +2,7 @@
 // balanced schedule (tok_pieces.h, step by step as tok_schedule takes it on the
 // device).
 //
-//   plan H B CAP          prints the plan: balanced (0 or 1), pieces, split, workspace bytes
+//   plan H B CAP [DV]     prints the plan: balanced (0 or 1), pieces, split, workspace bytes
 //   cut H B CAP           reads B lengths from stdin; prints "sequence first tokens" per piece
 //   sweep H               every batch with a balanced schedule, lengths to the capacity, equal and
 //                         mixed; prints "balanced plans, cuts, longest piece" and fails on a piece
@@ -81,8 +81,10 @@ int check(const std::vector<int>& len, int G, int heads) {
   return ok ? longest : -1;
 }
 
-bool plan_of(int heads, int B, int cap, DecodePlan* p) {
-  return make_decode_plan(layer(heads), B, cap, nullptr, p) == EG_MLA_OK;
+bool plan_of(int heads, int B, int cap, DecodePlan* p, int v_dim = 128) {
+  eg_mla_dims d = layer(heads);
+  d.v_head_dim = v_dim;
+  return make_decode_plan(d, B, cap, nullptr, p) == EG_MLA_OK;
 }
 
 int sweep(int heads) {
@@ -147,10 +149,10 @@ int server(char** v) {
 int main(int argc, char** argv) {
   if (argc == 10 && !std::strcmp(argv[1], "server")) return server(argv + 2);
   if (argc == 3 && !std::strcmp(argv[1], "sweep")) return sweep(std::atoi(argv[2]));
-  if (argc != 5) return 2;
+  if (argc != 5 && argc != 6) return 2;
   const int heads = std::atoi(argv[2]), B = std::atoi(argv[3]), cap = std::atoi(argv[4]);
   DecodePlan p;
-  if (!plan_of(heads, B, cap, &p)) return 2;
+  if (!plan_of(heads, B, cap, &p, argc == 6 ? std::atoi(argv[5]) : 128)) return 2;
   if (!std::strcmp(argv[1], "plan")) {
     std::printf("%d %d %d %zu\n", p.tok_balanced ? 1 : 0, p.pieces, p.split_tokens, p.bytes);
     return 0;
