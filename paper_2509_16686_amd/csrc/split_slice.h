@@ -198,7 +198,7 @@ constexpr int kFusedHeads = 2;  // heads per split: s_max >= 8
 // once the W_UK rows of all of a split's heads are in, it waits for nothing
 // between two heads.  (Left to it, it waited at the second head, and with that
 // for the first one's store: 340 cycles a work-group, and as many again in the
-// others' polls; 28 x 2048 18.8 -> 18.0 us per call.)
+// others' polls; 28 x 2048 18.7 -> 17.9 us per call.)
 __device__ __forceinline__ void wait_loads() {
   __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0)
 }
@@ -227,7 +227,8 @@ __device__ __forceinline__ void publish_stamp(const SplitArgs& a, int b, int hg,
 // kernel takes, measured slower: a range over two sequences pays the list,
 // first loads and merge twice in turn.)  256 sequences of 250 to 3901 tokens:
 // the kernel 72.5 -> 56 us; 48 of 250 to 4096: the call 34.1 -> 27.7 us.  The
-// schedule itself costs about 2 us, which the plan weighs (make_decode_plan).
+// schedule and a second work-group per compute unit cost up to 2 us, which the
+// plan weighs (make_decode_plan).
 // tok_schedule, run by one more work-group of the absorption launch, writes
 // each piece as (sequence, first token, tokens, 0) and each sequence's (first
 // row, rows).
@@ -238,80 +239,104 @@ struct TokSchedArgs {
   int2* seq_rows;  // [B]
 };
 
+// It has to be no longer than the absorption it runs beside: a thread holds two
+// sequences and two pieces, so that the loads, the prefix and the searches each
+// cost one round trip, and the search reads four keys at a time.  The launch
+// without it, with it as loops over single ones, and now: 384 sequences 5.2,
+// 9.2 and 6.0 us; 256 sequences 5.0, 6.2 and 5.2.
 template <int NT>
 __device__ __forceinline__ void tok_schedule(const TokSchedArgs& sa, int B) {
   static_assert(NT == 4 * kTokCandidates, "candidates x 4 quarters of the batch");
+  static_assert(kTokMaxBatch % 16 == 0 && kTokMaxBatch <= 2 * NT && kTokMaxPieces <= 2 * NT, "two of each per thread");
   __shared__ int len[kTokMaxBatch];
-  __shared__ int pre[kTokMaxBatch + 1];  // pieces before sequence b
-  __shared__ int wsum[NT / 64];
+  __shared__ __attribute__((aligned(16))) float key[kTokMaxBatch];  // 0 past the batch
+  __shared__ int pre[kTokMaxBatch];                                 // pieces before sequence b
+  __shared__ int wsum[2 * (NT / 64)];
+  __shared__ int wpre[NT / 64];
   __shared__ int cnt[NT];
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  int v = 0;
-  for (int b = tid; b < B; b += NT) {
-    const int L = clamp_len(sa.seq_lens[b], sa.cap);
-    len[b] = L;
-    v += L;
+  const int b0 = 2 * tid, b1 = b0 + 1;
+  const int r0 = b0 < B ? sa.seq_lens[b0] : 0, r1 = b1 < B ? sa.seq_lens[b1] : 0;
+  const int L0 = clamp_len(r0, sa.cap), L1 = clamp_len(r1, sa.cap);
+  if (b0 < kTokMaxBatch) {
+    len[b0] = L0;
+    len[b1] = L1;
+    key[b0] = tok_key(L0);
+    key[b1] = tok_key(L1);
   }
+  int v = L0 + L1, live = (L0 > 0 ? 1 : 0) + (L1 > 0 ? 1 : 0);  // tokens, sequences with any
 #pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o, 64);
-  if (lane == 0) wsum[w] = v;
+  for (int o = 32; o >= 1; o >>= 1) {
+    v += __shfl_xor(v, o, 64);
+    live += __shfl_xor(live, o, 64);
+  }
+  if (lane == 0) {
+    wsum[w] = v;
+    wsum[NT / 64 + w] = live;
+  }
   __syncthreads();
   const int N = wsum[0] + wsum[1] + wsum[2] + wsum[3];
+  const int firsts = wsum[4] + wsum[5] + wsum[6] + wsum[7];
   const TokSizes sizes = tok_sizes(N, sa.G, B);
   {
     const int c = tok_candidate(sizes, lane);
     const float rc = 1.f / static_cast<float>(c);
+    const int per = (B + 15) / 16;  // groups of 4 sequences per wave
+    const float4* k4 = reinterpret_cast<const float4*>(key) + w * per;
     int k = 0;
-#pragma unroll 8
-    for (int b = w; b < B; b += 4) k += tok_piece_count(len[b], c, rc);
+#pragma unroll 4
+    for (int i = 0; i < per; ++i) {
+      const float4 x = k4[i];
+      k += (tok_more_pieces(x.x, rc) + tok_more_pieces(x.y, rc)) + (tok_more_pieces(x.z, rc) + tok_more_pieces(x.w, rc));
+    }
     cnt[tid] = k;
   }
   __syncthreads();
-  const int total = cnt[lane] + cnt[64 + lane] + cnt[128 + lane] + cnt[192 + lane];
+  const int total = firsts + cnt[lane] + cnt[64 + lane] + cnt[128 + lane] + cnt[192 + lane];
   const uint64_t fits = __builtin_amdgcn_ballot_w64(total <= tok_candidate_limit(sa.G, lane));
   const int c = tok_candidate(sizes, tok_choice(fits));
   const float rc = 1.f / static_cast<float>(c);
-  int carry = 0;
-  for (int base = 0; base < B; base += NT) {
-    const int b = base + tid;
-    const int k = b < B ? tok_piece_count(len[b], c, rc) : 0;
-    int x = k;
+  const int k0 = tok_piece_count(L0, rc), k1 = tok_piece_count(L1, rc);
+  int x = k0 + k1;
 #pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-      const int y = __shfl_up(x, o, 64);
-      if (lane >= o) x += y;
-    }
-    __syncthreads();
-    if (lane == 63) wsum[w] = x;
-    __syncthreads();
-    int before = carry;
-#pragma unroll
-    for (int i = 0; i < NT / 64; ++i) {
-      if (i < w) before += wsum[i];
-      carry += wsum[i];
-    }
-    if (b < B) {
-      pre[b] = before + x - k;
-      sa.seq_rows[b] = make_int2(before + x - k, k);
-    }
+  for (int o = 1; o < 64; o <<= 1) {
+    const int y = __shfl_up(x, o, 64);
+    if (lane >= o) x += y;
   }
+  if (lane == 63) wpre[w] = x;
   __syncthreads();
-  for (int g = tid; g < sa.G; g += NT) {
-    int4 r = make_int4(0, 0, 0, 0);  // no tokens
-    if (g < carry) {
-      int l = 0, h = B;  // the last sequence whose first piece is at most g (empty ones have no piece)
-      while (h - l > 1) {
-        const int mid = (l + h) >> 1;
-        if (pre[mid] <= g) l = mid;
-        else h = mid;
-      }
-      const int L = len[l], k = tok_piece_count(L, c, rc);
-      const int size = tok_piece_tokens(L, k);
-      const int t0 = (g - pre[l]) * size;
-      r = make_int4(l, t0, min(size, L - t0), 0);
-    }
-    sa.pieces[g] = r;
+  int before = x - k0 - k1, pieces = 0;
+#pragma unroll
+  for (int i = 0; i < NT / 64; ++i) {
+    if (i < w) before += wpre[i];
+    pieces += wpre[i];
   }
+  if (b0 < kTokMaxBatch) {
+    pre[b0] = before;
+    pre[b1] = before + k0;
+  }
+  if (b0 < B) sa.seq_rows[b0] = make_int2(before, k0);
+  if (b1 < B) sa.seq_rows[b1] = make_int2(before + k0, k1);
+  __syncthreads();
+  // pieces tid and tid + NT: the last sequence whose first piece is at most that (empty ones have no piece)
+  int s0 = 0, s1 = 0;
+  for (int n = B; n > 1;) {
+    const int half = n / 2;
+    const int p0 = pre[s0 + half], p1 = pre[s1 + half];
+    s0 += p0 <= tid ? half : 0;
+    s1 += p1 <= tid + NT ? half : 0;
+    n -= half;
+  }
+  auto put = [&](int g, int b) {
+    int4 r = make_int4(0, 0, 0, 0);  // no tokens
+    if (g < pieces) {
+      const int L = len[b], size = tok_piece_tokens(L, tok_piece_count(L, rc)), t0 = (g - pre[b]) * size;
+      r = make_int4(b, t0, min(size, L - t0), 0);
+    }
+    if (g < sa.G) sa.pieces[g] = r;
+  };
+  put(tid, s0);
+  put(tid + NT, s1);
 }
 
 template <int DC, int DR, int NW, int D, int SL, bool FUSED = false, bool BAL = false>

@@ -40,13 +40,15 @@ constexpr int tok_choice(uint64_t fits) {
   if (fits >> kTokEvenLane) return kTokEvenLane;
   return fits ? __builtin_ctzll(fits) : kTokEvenLane - 1;
 }
-// Pieces of a sequence of L tokens: ceil(L / c), exact for lengths below 2^24 (rc = 1 / c).
-constexpr int tok_piece_count(int L, int c, float rc) {
-  const int x = L + c - 1;
-  const int q = static_cast<int>(static_cast<float>(x) * rc);
-  const int r = x - q * c;
-  return q + (r >= c ? 1 : 0) - (r < 0 ? 1 : 0);
-}
+// Pieces of a sequence of L > 0 tokens beyond its first, ceil(L / c) - 1, from
+// tok_key(L) and rc = 1 / c.  (L - 1/2) / c is at least 1 / (2 c) away from any
+// whole number, more than the two roundings move it for L below 2^22, so three
+// instructions do.  (The search of tok_schedule runs this for every sequence and
+// candidate; with an integer quotient and its corrections the launch that holds
+// it took 1.2 us more for 384 sequences.)
+constexpr float tok_key(int L) { return L > 0 ? static_cast<float>(L) - 0.5f : 0.f; }
+constexpr int tok_more_pieces(float key, float rc) { return static_cast<int>(key * rc); }
+constexpr int tok_piece_count(int L, float rc) { return L > 0 ? 1 + tok_more_pieces(tok_key(L), rc) : 0; }
 // Tokens of each of its k > 0 pieces (the last may have fewer): at most c, so
 // that the k - 1 first pieces stay below L.
 constexpr int tok_piece_tokens(int L, int k) { return ((L + k - 1) / k + 15) & ~15; }

@@ -12,6 +12,11 @@ def test_pieces_fit_the_token_list(tok_pieces, heads):
     assert plans > 0 and cuts == 7 * plans and longest <= TOKEN_LIST
 
 
+def test_piece_counts_are_quotients(tok_pieces):
+    """The float piece count equals the integer one for every piece size, around every multiple of it."""
+    assert tok_pieces("quotients") == [(0,)]
+
+
 @pytest.mark.parametrize("batch,length", [(40, 25000), (60, 20000), (64, 20000), (62, 28000), (128, 10000),
                                           (48, 24000), (40, 28672)])
 def test_long_batches(tok_pieces, batch, length):

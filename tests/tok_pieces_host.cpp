@@ -7,6 +7,7 @@
 //   sweep H               every batch with a balanced schedule, lengths to the capacity, equal and
 //                         mixed; prints "balanced plans, cuts, longest piece" and fails on a piece
 //                         beyond the token list, too many pieces or tokens not covered once
+//   quotients             tok_piece_count against integer division; fails on a difference
 //   server H DH DV DC DR DTYPE B CAP
 //                         batches up to B that one workspace, sized for B, holds and that plans
 //                         with the most rows fit: "batches fitting of them, all fitting"
@@ -48,14 +49,14 @@ std::vector<Piece> cut(const std::vector<int>& len, int G) {
     const int c = tok_candidate(sizes, lane);
     const float rc = 1.f / static_cast<float>(c);
     int k = 0;
-    for (int L : len) k += tok_piece_count(L, c, rc);
+    for (int L : len) k += tok_piece_count(L, rc);
     if (k <= tok_candidate_limit(G, lane)) fits |= uint64_t{1} << lane;
   }
   const int c = tok_candidate(sizes, tok_choice(fits));
   const float rc = 1.f / static_cast<float>(c);
   std::vector<Piece> out;
   for (int b = 0; b < B; ++b) {
-    const int k = tok_piece_count(len[b], c, rc);
+    const int k = tok_piece_count(len[b], rc);
     if (k <= 0) continue;
     const int size = tok_piece_tokens(len[b], k);
     for (int i = 0; i < k; ++i) out.push_back({b, i * size, std::min(size, len[b] - i * size)});
@@ -121,6 +122,22 @@ int sweep(int heads) {
   return 0;
 }
 
+// tok_piece_count against the integer quotient: every multiple of the step of 16 up to the list, lengths around
+// every multiple of it and the largest.
+int quotients() {
+  for (int c = 16; c <= kMaxSliceSplitTokens; c += 16) {
+    const float rc = 1.f / static_cast<float>(c);
+    for (int64_t m = 0; m <= (1 << 22); m += c)
+      for (int d = -1; d <= 1; ++d) {
+        const int64_t L = m + d;
+        if (L < 0 || L >= (1 << 22)) continue;
+        if (tok_piece_count(static_cast<int>(L), rc) != (L + c - 1) / c) return 1;
+      }
+  }
+  std::printf("0\n");
+  return 0;
+}
+
 int server(char** v) {
   eg_mla_dims d = layer(std::atoi(v[0]));
   d.head_dim = std::atoi(v[1]);
@@ -147,6 +164,7 @@ int server(char** v) {
 }  // namespace
 
 int main(int argc, char** argv) {
+  if (argc == 2 && !std::strcmp(argv[1], "quotients")) return quotients();
   if (argc == 10 && !std::strcmp(argv[1], "server")) return server(argv + 2);
   if (argc == 3 && !std::strcmp(argv[1], "sweep")) return sweep(std::atoi(argv[2]));
   if (argc != 5 && argc != 6) return 2;
