@@ -425,7 +425,8 @@ __global__ __launch_bounds__(256 * KG, 2) void append_gemm_kernel(const uint16_t
   uint16_t(*stage)[kGemmRows * C::STRIDE] = reinterpret_cast<uint16_t(*)[kGemmRows * C::STRIDE]>(lds);
   const int ks = blockIdx.x, tt = blockIdx.y, ot = blockIdx.z;
   const int tid = threadIdx.x, lane = tid & 63, r32 = lane & 31, h = lane >> 5;
-  const int w8 = __builtin_amdgcn_readfirstlane(tid >> 6), w = w8 & 3, kg = w8 >> 2;
+  const int w8 = KG > 1 ? __builtin_amdgcn_readfirstlane(tid >> 6) : tid >> 6;
+  const int w = KG > 1 ? w8 & 3 : w8, kg = KG > 1 ? w8 >> 2 : 0;
   const int wt = w & 1, wo = w >> 1;
   const int64_t kb = static_cast<int64_t>(slice) * ks;
   // copy j = tid + THREADS i: row j / PIECES (token rows first, then W_DKV rows), 16 bytes at 8 (j % PIECES)
@@ -505,14 +506,15 @@ __global__ __launch_bounds__(256 * KG, 2) void append_gemm_kernel(const uint16_t
 #pragma unroll
     for (int ob = 0; ob < 3; ++ob)
 #pragma unroll
-      for (int q = 0; q < 4; ++q)
-        *reinterpret_cast<f32x4_t*>(row + 32 * ob + 8 * q) =
-            f32x4_t{a[ob][4 * q], a[ob][4 * q + 1], a[ob][4 * q + 2], a[ob][4 * q + 3]} + other(4 * ob + q);
+      for (int q = 0; q < 4; ++q) {
+        f32x4_t v = {a[ob][4 * q], a[ob][4 * q + 1], a[ob][4 * q + 2], a[ob][4 * q + 3]};
+        if constexpr (KG > 1) v += other(4 * ob + q);
+        *reinterpret_cast<f32x4_t*>(row + 32 * ob + 8 * q) = v;
+      }
   };
   if constexpr (KG == 1) {
-    auto none = [](int) { return f32x4_t{0.f, 0.f, 0.f, 0.f}; };
-    store(0, acc[0], none);
-    store(1, acc[1], none);
+    store(0, acc[0], 0);
+    store(1, acc[1], 0);
   } else {
     // group kg stores token block kg of its tile and hands the other one over
     // (the stage is free: the loop ended in a barrier)
