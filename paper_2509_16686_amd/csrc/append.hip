@@ -295,6 +295,7 @@ __global__ __launch_bounds__(256) void append_mfma_kernel(const uint16_t* __rest
 // stored.
 // ---------------------------------------------------------------------------
 constexpr int kAppSliceUnit = 256;    // slice widths are multiples of this
+constexpr int kAppCus = 256;          // compute units
 #ifndef EGMLA_APPEND_TARGET_GROUPS
 #define EGMLA_APPEND_TARGET_GROUPS 512
 #endif
@@ -396,8 +397,8 @@ __global__ __launch_bounds__(256) void append_slice_kernel(const uint16_t* __res
 // What bounds it: a step is a chain of operand reads, 12 products per wave, LDS
 // writes and a barrier (about 1100 cycles, 384 of them products), with one
 // work-group per compute unit.  KG = 2 puts two waves on a SIMD and reads whole
-// 128-byte lines; at d_c 512, hidden 7168 the call went from 55.9 to 48.4 us at
-// 4096 tokens, 98.5 to 83.9 at 8192, 34.2 to 31.6 at 2048.  The d_c 128 layer's
+// 128-byte lines; at d_c 512, hidden 7168 the call went from 55.3 to 49.4 us at
+// 4096 tokens, 98.5 to 87.1 at 8192, 34.1 to 31.6 at 2048.  The d_c 128 layer's
 // slices are 1 to 4 steps long there, and the addition costs more than that
 // gains (1024 tokens 15.3 us with KG = 1, 15.9 with 2).  Cutting the work into
 // equal runs across tiles instead of slices (one per compute unit) lost more to
@@ -774,8 +775,14 @@ extern "C" eg_mla_status eg_mla_append_ws(const eg_mla_dims* dims, int32_t n_tok
     hipLaunchKernelGGL((append_finish_kernel<128, 64, 64>), dim3((n_tokens + 3) / 4), dim3(256), 0, stream, part,
                        nks, token_ids, positions, slots, nw, theta, cb, token_id_cache, num_slots, n_tokens);
   } else {
-    // slices of one unit (few tokens) are too short for two groups: 256 tokens 19.2 us with one, 20.0 with two
-    if (gemm && slice > kAppSliceUnit) pass1(append_gemm_kernel<576, 2>, GemmCfg<2>::THREADS);
+    // Two groups from slices of three units on (us per call with one group / two: hidden 7168, 700 tokens, slice 512
+    // 25.4 / 26.7; hidden 5376, 3000, slice 1792 35.9 / 34.8), but where the work-groups are more than the compute
+    // units, of which two-group ones take one each, only where long slices outweigh the second round (hidden 2304,
+    // 4096 tokens, 288 work-groups, slice 768 34.9 / 37.3; 6400, 2500, 300, 1280 58.2 / 60.4; 2048, 11000, 258, 2048
+    // 67.5 / 65.2).
+    const int64_t wgs = static_cast<int64_t>(grid1.x) * grid1.y * grid1.z;
+    const bool two = gemm && slice >= 3 * kAppSliceUnit && (wgs <= kAppCus || slice >= 2048);
+    if (two) pass1(append_gemm_kernel<576, 2>, GemmCfg<2>::THREADS);
     else if (gemm) pass1(append_gemm_kernel<576, 1>, GemmCfg<1>::THREADS);
     else if (per == 32) pass1(append_slice_kernel<576, 1>, 256);
     else pass1(append_slice_kernel<576, 2>, 256);

@@ -164,8 +164,11 @@ def test_append_token_counts(gpu, wi, entry, n):
 
 @pytest.mark.parametrize("hidden,n", [
     (256, 256),      # one unit of 256 k: one group
-    (512, 11009),    # the shortest slice of two groups; a ragged last tile of one token
+    (512, 11009),    # two units: one group; a ragged last tile of one token
+    (768, 5505),     # the shortest slice of two groups
     (1792, 5505),    # seven units in one slice
+    (1792, 11009),   # ... of more work-groups than compute units: one group
+    (2048, 11009),   # ... and long enough for two all the same
 ])
 def test_append_two_group_product(gpu, hidden, n):
     # the d_c 512 layer's tiled product (two groups of waves share a tile's k) at other widths
