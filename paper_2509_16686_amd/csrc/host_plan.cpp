@@ -20,17 +20,18 @@ constexpr int kMaxPartialsTok = 128;
 constexpr int kMergeValueDim = 128;  // value dim of the MFMA merge kernels (run_decode)
 constexpr int kMinSplitTok = 64;
 // The d_c 128 kernel takes the balanced schedule from this capacity on, where a
-// (sequence, split) item is long enough to pay for the schedule (about 2 us):
+// (sequence, split) item is long enough to pay for the schedule and the second
+// work-group per compute unit (up to 2 us):
 // from kTokBalancedUneven tokens if the items do not fit one per compute unit
 // (some then run two, and the balanced pieces win at equal lengths too), else
 // only from kTokBalancedEven, where the longest sequences set the time.
 // Measured, us per call without / with, lengths n / 16 to n and all n:
-//   72 x 1900 (544-token items, 288 of them)  30.2 / 26.7, 33.4 / 31.5
-//   200 x 1900 (two items a sequence, 400)    55.4 / 38.1, 60.6 / 52.5
-//   96 x 1000 (384, 288)                      25.2 / 21.8, 27.4 / 28.5
-//   64 x 4000 (1024, 256)                     30.5 / 30.4, 36.4 / 37.6
-//   128 x 1000 (512, 256)                     23.5 / 26.0, 26.5 / 28.4
-//   256 x 1900 (1920, 256)                    47.0 / 43.1, 57.6 / 58.2
+//   72 x 1900 (544-token items, 288 of them)  29.4 / 25.7, 32.9 / 30.7
+//   200 x 1900 (two items a sequence, 400)    53.0 / 36.5, 59.2 / 50.8
+//   96 x 1000 (384, 288)                      25.2 / 21.3, 27.3 / 27.3
+//   64 x 4000 (1024, 256)                     29.8 / 29.9, 35.3 / 37.0
+//   128 x 1000 (512, 256)                     23.3 / 25.0, 26.6 / 27.6
+//   256 x 1900 (1920, 256)                    45.5 / 41.3, 55.3 / 56.7
 constexpr int kTokBalancedMinCap = 1024;
 constexpr int kTokBalancedUneven = 448;
 constexpr int kTokBalancedEven = 1920;

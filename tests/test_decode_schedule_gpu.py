@@ -26,14 +26,15 @@ def lens_mix(batch, top, seed):
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("batch,heads,top", [
-    (33, 16, 1024),    # short items: (sequence, split) ones
-    (40, 32, 4100),    # two head groups share each piece
-    (64, 16, 9000),    # one long sequence: pieces of the search's upper end
-    (384, 16, 1100),   # the largest balanced batch
-    (385, 16, 1100),   # past it: one item per sequence
+@pytest.mark.parametrize("batch,heads,top,balanced", [
+    (33, 16, 1024, False),   # short items: (sequence, split) ones
+    (40, 32, 4100, True),    # two head groups share each piece
+    (64, 16, 9000, True),    # one long sequence among short ones
+    (384, 16, 1100, True),   # the largest balanced batch
+    (385, 16, 1100, False),  # past it: one item per sequence
 ])
-def test_balanced_schedule(gpu, batch, heads, top):
+def test_balanced_schedule(gpu, tok_pieces, batch, heads, top, balanced):
+    assert tok_pieces("plan", heads, batch, -(-top // 16) * 16)[0][0] == balanced
     wl = W.WORKLOADS[1].replace(name="balanced", batch=batch, heads=heads, vocab=3000, seq_len=None,
                                 seq_len_range=(0, top), page_size=16, paged=True, seed=5)
     inp = W.generate(wl, seq_lens=lens_mix(batch, top, batch))
@@ -49,12 +50,13 @@ def test_balanced_schedule(gpu, batch, heads, top):
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("batch,top", [
-    (72, 1600),     # 288 items of 480 tokens: balanced
-    (64, 1728),     # 256 items of 448: not
-    (256, 1920),    # 256 items of 1920: balanced
+@pytest.mark.parametrize("batch,top,balanced", [
+    (72, 1600, True),     # 288 items of 480 tokens
+    (64, 1728, False),    # 256 items of 448
+    (256, 1920, True),    # 256 items of 1920
 ])
-def test_balanced_rule(gpu, batch, top):
+def test_balanced_rule(gpu, tok_pieces, batch, top, balanced):
+    assert tok_pieces("plan", 16, batch, top)[0][0] == balanced
     wl = W.WORKLOADS[1].replace(name="balanced", batch=batch, vocab=3000, seq_len=None, seq_len_range=(0, top),
                                 page_size=16, paged=True, seed=7)
     inp = W.generate(wl, seq_lens=lens_mix(batch, top, batch))
