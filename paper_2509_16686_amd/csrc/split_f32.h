@@ -307,7 +307,7 @@ __global__ __launch_bounds__(NW * 64, DCM <= 128 ? 2 : 1) void split_f32_kernel(
 #pragma unroll
       for (int q = 0; q < 4; ++q) x[q] = 4 * g + q < nt ? s0[q] * a.scale_log2 : -INFINITY;
       const float mt = max_over_row_groups(fmaxf(fmaxf(x[0], x[1]), fmaxf(x[2], x[3])));
-      const float m_new = fmaxf(m_run, mt);  // finite: the unit has a valid token
+      const float m_new = fmaxf(m_run, mt);
       const bool grow = m_new > m_run + kLazyRescale;
       if (__builtin_amdgcn_ballot_w64(grow)) {
         const float alpha = grow ? exp2f(m_run - m_new) : 1.0f;  // exp2(-inf) = 0
@@ -316,10 +316,12 @@ __global__ __launch_bounds__(NW * 64, DCM <= 128 ? 2 : 1) void split_f32_kernel(
 #pragma unroll
         for (int db = 0; db < NB; ++db) o[db] *= alpha;
       }
+      // (-inf only while every score so far overflowed to it: those tokens weigh nothing)
+      const float m_ref = m_run == -INFINITY ? 0.f : m_run;
       float p[4];
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
-        p[q] = exp2f(x[q] - m_run);
+        p[q] = exp2f(x[q] - m_ref);
         l_run += p[q];
       }
 #pragma unroll

@@ -54,3 +54,25 @@ def test_f32_plan_needs_no_more_workspace(shape, batch, cap):
     auto = B.decode_workspace_size(d, batch, pages)
     assert 0 < auto <= B.decode_workspace_size(d, batch, pages, B.make_plan(B.PATH_VALU))
     assert B.decode_workspace_size(d, batch, pages, B.make_plan(B.PATH_MFMA)) == 0
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dt,n", [("fp32", 300), ("fp32", 700), ("bf16", 300), ("bf16", 700)])
+def test_tokens_of_infinitely_low_score(gpu, dt, n):
+    """A block of tokens whose scores overflow to -inf weighs nothing, also where it fills whole units of a wave (and
+    not a whole 32-token tile of the vector kernel, which is the reference here)."""
+    import torch
+    wl = workload((dt, 4, 32, 32, 32, 8), np.array([n]), paged=False)
+    dd = B.stage_decode(W.generate(wl, seq_lens=np.array([n])))
+    dd.q[..., -8:] = dd.q[..., -8:].abs() + 2
+    dd.cache[:16, -8:] = -3e38   # the first unit of the first wave
+    dd.cache[80:96, -8:] = -3e38  # a later one
+    say(f"decode -inf scores {dt} n={n}")
+    got = B.run_decode(dd).double()
+    ref_out = torch.empty_like(dd.out)
+    dd.out = ref_out
+    ref = B.run_decode(dd, plan=B.make_plan(B.PATH_VALU)).double()
+    torch.cuda.synchronize()
+    assert torch.isfinite(ref).all() and torch.isfinite(got).all()
+    # fp32 sums in another order; bf16 outputs also round differently
+    assert (got - ref).norm() <= (1e-5 if dt == "fp32" else 5e-3) * ref.norm()
