@@ -166,10 +166,12 @@ __global__ __launch_bounds__(NW * 64, 2) void split_rows_kernel(SplitArgs a) {
 #pragma unroll
         for (int db = 0; db < NB; ++db) o[db] *= alpha;
       }
+      // (-inf only while every score so far overflowed to it: those tokens weigh nothing)
+      const float m_ref = m_run == -INFINITY ? 0.f : m_run;
       float p[4];
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
-        p[q] = __builtin_amdgcn_exp2f(x[q] - m_run);
+        p[q] = __builtin_amdgcn_exp2f(x[q] - m_ref);
         l_run += p[q];
       }
       const f16x4_t pb = __builtin_bit_cast(f16x4_t, u32x2_t{pack_f16x2(p[0], p[1]), pack_f16x2(p[2], p[3])});
