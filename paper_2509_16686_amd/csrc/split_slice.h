@@ -701,7 +701,7 @@ __global__ __launch_bounds__(NW * 64, 2) void split_slice_kernel(SplitArgs a) {
           if (4 * g + q >= nt) x[q] = -INFINITY;
       }
       const float mt = max_over_row_groups(fmaxf(fmaxf(x[0], x[1]), fmaxf(x[2], x[3])));
-      const float m_new = fmaxf(m_run, mt);  // finite: the unit has a valid token
+      const float m_new = fmaxf(m_run, mt);
       const bool grow = m_new > m_run + kLazyRescale;  // false while both are -inf
       if (__builtin_amdgcn_ballot_w64(grow)) {
         const float alpha = grow ? __builtin_amdgcn_exp2f(m_run - m_new) : 1.0f;  // exp2(-inf) = 0
@@ -710,10 +710,12 @@ __global__ __launch_bounds__(NW * 64, 2) void split_slice_kernel(SplitArgs a) {
 #pragma unroll
         for (int db = 0; db < NB; ++db) o[db] *= alpha;
       }
+      // (-inf only while every score so far overflowed to it: those tokens weigh nothing)
+      const float m_ref = m_run == -INFINITY ? 0.f : m_run;
       float p[4];
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
-        p[q] = __builtin_amdgcn_exp2f(x[q] - m_run);  // masked: exp2(-inf) = 0
+        p[q] = __builtin_amdgcn_exp2f(x[q] - m_ref);  // masked: exp2(-inf) = 0
         l_run += p[q];
       }
       const f16x4_t pb = __builtin_bit_cast(f16x4_t, u32x2_t{pack_f16x2(p[0], p[1]), pack_f16x2(p[2], p[3])});

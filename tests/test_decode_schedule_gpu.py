@@ -123,6 +123,27 @@ def test_short_splits(gpu, lens):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("batch,n", [(1, 300), (8, 2000), (40, 4100)])  # short splits, shared absorption, balanced
+def test_tokens_of_infinitely_low_score(gpu, batch, n):
+    """A unit of 16 tokens whose RoPE scores overflow to -inf weighs nothing, wherever a split or piece has it; the
+    vector kernel is the reference."""
+    import torch
+    wl = W.WORKLOADS[1].replace(batch=batch, vocab=700, seq_len=n, page_size=4, paged=False, seed=4)
+    dd = B.stage_decode(W.generate(wl, seq_lens=np.full(batch, n, dtype=np.int32)))
+    dd.q[..., -64:] = dd.q[..., -64:].abs() + 2
+    rows = dd.cache.view(batch, n, -1)
+    for at in (64, 160, 256):
+        rows[:, at:at + 16, -64:] = -3e38
+    say(f"decode -inf scores B={batch} n={n}")
+    got = B.run_decode(dd).double()
+    dd.out = torch.empty_like(dd.out)
+    ref = B.run_decode(dd, plan=B.make_plan(B.PATH_VALU)).double()
+    torch.cuda.synchronize()
+    assert torch.isfinite(ref).all() and torch.isfinite(got).all()
+    assert (got - ref).norm() <= 5e-3 * ref.norm()  # bf16 outputs, fp16 latent operands on one side
+
+
+@pytest.mark.gpu
 @pytest.mark.parametrize("wl,most,batch,top", [
     (W.WORKLOADS[1], 256, 100, 4096),           # balanced pieces do not fit the workspace of 256 sequences
     (W.WORKLOADS[1], 64, 40, 4096),
