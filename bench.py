@@ -43,15 +43,17 @@ MODEL_LAYERS = 24
 
 def split_kernel_name(wl, path):
     """The split kernel the library launches for this workload and path (see host_plan.cpp)."""
-    if wl.dtype != "bf16" or path == "valu":
+    if path == "valu":
         return "split_valu_kernel"
-    if wl.latent_dim == 128 and wl.rope_dim == 64:
-        return "split_slice_kernel"
-    if wl.latent_dim == 512 and wl.rope_dim == 64 and wl.heads % 128 == 0:
-        return "split_wide_kernel"
-    if wl.heads % 16 == 0 and wl.rope_dim == 64 and wl.latent_dim in (320, 512):
-        return "split_mfma_kernel"
-    return "split_valu_kernel"
+    if wl.dtype == "bf16" and wl.heads % 16 == 0 and wl.rope_dim == 64:
+        if wl.latent_dim == 128:
+            return "split_slice_kernel"
+        if wl.latent_dim == 320:
+            return "split_rows_kernel"
+        if wl.latent_dim == 512:
+            wide = wl.heads % 64 == 0 and wl.head_dim == 128 and wl.v_head_dim == 128
+            return "split_wide_kernel" if wide else "split_mfma_kernel"
+    return "split_f32_kernel" if wl.latent_dim <= 320 and wl.rope_dim <= 64 else "split_valu_kernel"
 
 def recorded_traffic():
     """Bytes per split-kernel launch from the committed counter summary, or None when the

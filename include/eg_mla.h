@@ -338,11 +338,12 @@ eg_mla_status eg_mla_prefill_ref(const eg_mla_dims* dims, int32_t seq_len, const
  *       (rows as eg_mla_append writes them); token_ids [total];
  *   gate_table, w_uk, w_uv as for decode;  out [total, H, d_v].
  *   workspace: eg_mla_prefill_varlen_workspace_size bytes, 256-byte aligned
- *       (per-token sequence starts; absorbed form: the absorbed queries
- *       [T][H][d_c + d_r] (q_lat fp16, q^R bf16), the normalised latent
- *       outputs in fp16 [T][H][d_c] and the gated latents in fp16 [T][d_c];
- *       explicit form: K^C and V in fp16, [H][T][128] each, and the gated
- *       latents as bf16 hi and lo rows, [T][d_c] each).
+ *       (per-token sequence starts; absorbed form: the absorbed queries in
+ *       fp16 [T][H][d_c] and, in the room of T H d_r more values after them,
+ *       the attention blocks' order, then the normalised latent outputs in
+ *       fp16 [T][H][d_c] and the gated latents in fp16 [T][d_c]; explicit
+ *       form: K^C and V in fp16, [H][T][128] each, and the gated latents as
+ *       bf16 hi and lo, [T][d_c] each, in the projection's step order).
  * Pointers 16-byte aligned.  total_tokens == 0 is a no-op.
  * ------------------------------------------------------------------------- */
 size_t eg_mla_prefill_varlen_workspace_size(const eg_mla_dims* dims, int32_t total_tokens);
