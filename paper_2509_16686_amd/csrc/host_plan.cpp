@@ -13,9 +13,9 @@ constexpr int kTargetWorkItems = 1024;
 // longest without gaps between its loads (256 compute units).
 constexpr int kTargetWorkItemsTok = 256;
 // ... and its smallest automatic split, one unit for each of its four waves
-// (measured with few sequences: 8 of 203 to 2000 tokens 14.9 us per call with
-// 64-token splits, 16.9 with 256), while the partials of a sequence stay few
-// (1 x 32768: 18.7 us with 128 partials, 19.8 with 256).
+// (measured with few sequences: 8 of 1000 tokens 13.8 us per call with 64-token
+// splits, 16.3 with 256), while the partials of a sequence stay few (1 x 32768:
+// 18.7 us with 128 partials, 19.8 with 256).
 constexpr int kMaxPartialsTok = 128;
 constexpr int kMergeValueDim = 128;  // value dim of the MFMA merge kernels (run_decode)
 constexpr int kMinSplitTok = 64;
@@ -152,20 +152,25 @@ eg_mla_status make_decode_plan(const eg_mla_dims& d, int32_t batch, int32_t max_
       const int cap = std::max(p.capacity, 1);
       auto cut = [&](int n) { return std::max(kMinSplitTok, ceil_div(cap, n * kTile) * kTile); };
       // Short splits only where the items still run one per compute unit (48 x
-      // 1000: 288 items of 192 tokens 18.8 us per call, 192 of 256 17.1), and
-      // 16 or 8 a sequence rather than some number between: the absorption is
-      // then shared evenly, and 8 partials merge in small work-groups.  With up
-      // to 16 sequences the splits above come to at most 16.  With more, 8 up
-      // to 192 tokens (us per call: as above / 8 splits / of 256 tokens):
+      // 1000: 288 items of 192 tokens 18.8 us per call, 192 of 256 17.1); up to
+      // 4 sequences of 4096 no more than 32 a sequence, which the kernel can
+      // absorb the query with (below; 4 x 4096: 32 splits of 128 15.1 us in a
+      // graph, 64 of 64 and a launch more 14.5, but a host needs 13 to 17 to
+      // enqueue its three launches, 10.5 to 12 for two).  With 17 to 32 sequences 8 a
+      // sequence rather than some number between 8 and 16: the absorption is
+      // then shared evenly, and 8 partials merge in small work-groups; up to 192
+      // tokens each (us per call: as above / 8 splits / of 256 tokens):
       //   20 x 1300  17.6 / 16.1 / 17.2    24 x 1500  18.3 / 16.6 / 17.3
       //   28 x 1100  18.0 / 16.5 / 17.3    20 x 900   16.6 / 15.9 / 17.0
       // and 256 tokens from there to 2048 (24 x 1600 18.2 / 17.7 / 17.3, 28 x
       // 1800 19.9 / 18.6 / 18.7); above, more than 8 splits are due anyway
       // (20 x 2300 18.1 / 18.7 / 19.1).
-      if (per_split > 16 && 8 * per_split <= kTargetWorkItemsTok && cap <= 8 * 256)
+      if (per_split <= 4 && cap <= 32 * 128)
+        s = std::max<int64_t>(s, cut(32));
+      else if (per_split > 16 && 8 * per_split <= kTargetWorkItemsTok && cap <= 8 * 256)
         s = cut(8) <= 192 ? cut(8) : 256;
       else if (per_split * ceil_div(cap, static_cast<int>(s)) > kTargetWorkItemsTok)
-        s = per_split <= 16 && cut(16) < 256 ? cut(16) : 256;  // (12 x 2048: 264 items; 16 splits 15.5, of 256 tokens 17.5)
+        s = per_split <= 16 && cut(16) < 256 ? cut(16) : 256;  // (12 x 2048, not 264 items: 16 splits 15.7, 256 tokens 17.0)
     }
     s = std::min<int64_t>(s, max_split);
     split = static_cast<int>(s);
@@ -189,15 +194,22 @@ eg_mla_status make_decode_plan(const eg_mla_dims& d, int32_t batch, int32_t max_
   const size_t H = static_cast<size_t>(d.num_heads);
   const size_t DQ = static_cast<size_t>(d.latent_dim + d.rope_dim);
   // The split kernel absorbs the query itself when that costs each work-group
-  // at most 2 heads' W_UK (8 to 16 splits per sequence, every split a
-  // producer) and every work-group is resident at once (2 per compute unit);
+  // at most 2 heads' W_UK (8 or more splits per sequence, the first 16 of them
+  // producers) and every work-group is resident at once (2 per compute unit);
   // otherwise (many splits, whose extra work-groups only wait, or a batch of
   // several rounds of work-groups each reading 4 or more heads' W_UK) the
   // absorption kernel runs first (measured: B32 L4096 25.2 against 25.7 us
-  // per call; B4 L32768 28.9 against 27.8; B256 L2048 70.8 against 59.4).
+  // per call; B4 L32768 28.9 against 27.8; B256 L2048 70.8 against 59.4).  Of
+  // 17 to 32 splits the short ones take it, where waiting for the producers
+  // costs no more than the launch they save: the two run about as long (2 x
+  // 1856 13.6 / 13.7 us in a graph, 12 x 1280 14.7 / 14.5; 8 x 3000, 256 items,
+  // 16.0 / 15.4), but a step of append and decode is then four launches, not
+  // five, and a host has to enqueue them: 2 x 1856 22.9 us against 25.7.
   const int64_t nblk = static_cast<int64_t>(std::max(batch, 0)) * p.s_max * p.head_groups;
-  p.fused_absorb = sliced_kernel && p.slices == 1 && d.head_dim == 128 && p.s_max >= 8 && p.s_max <= 16 &&
-                   nblk <= 2 * kTargetWorkItemsTok;
+  const bool short_splits = unit_kernel && (plan == nullptr || plan->split_tokens == 0) && p.s_max <= 32 &&
+                            (p.split_tokens <= kMinSplitTok || (p.split_tokens <= 128 && nblk <= 224));
+  p.fused_absorb = sliced_kernel && p.slices == 1 && d.head_dim == 128 && p.s_max >= 8 &&
+                   (p.s_max <= 16 || short_splits) && nblk <= 2 * kTargetWorkItemsTok;
   auto layout = [&]() {
     const size_t rows = p.balanced       ? kWideMaxGroups + B
                         : p.tok_balanced ? static_cast<size_t>(p.pieces)

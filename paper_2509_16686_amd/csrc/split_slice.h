@@ -177,10 +177,10 @@ __device__ __forceinline__ void absorb_head_128(const SplitArgs& a, int b, int h
   absorb_finish(a, b, h, r, red);
 }
 
-// FUSED (no id slices, d_h = 128, 8 to 16 splits per sequence): the
+// FUSED (no id slices, d_h = 128, 8 to 32 splits per sequence): the
 // work-groups of a sequence also absorb its query.  Split s of the s_max splits
-// of sequence b absorbs the heads j (of its group of 16) with j = s mod s_max,
-// whether or not it holds tokens (with the heads spread over the non-empty
+// of sequence b absorbs the heads j (of its group of 16) with j = s mod s_max
+// (none from split 16 on), whether or not it holds tokens (with the heads spread over the non-empty
 // splits only, the one split of a short sequence absorbed all 16 in turn: the
 // whole call 27.5 against 16.9 us for 8 sequences of 203 to 2000 tokens in
 // 256-token splits): their W_UK rows load
@@ -189,7 +189,7 @@ __device__ __forceinline__ void absorb_head_128(const SplitArgs& a, int b, int h
 // (vector memory operations complete in issue order, so the stores are then
 // complete) the work-group publishes the call's stamp in qflags[b][group][s];
 // an empty split then ends.  Before its first scores a work-group waits for
-// the stamps of all s_max splits (they run at the same time: at most two
+// the stamps of the first 16 splits (they run at the same time: at most two
 // work-groups per compute unit), polling at most spin_limit times; if one is
 // missing it absorbs all 16 heads itself (the same bits), so the wait always
 // ends.
@@ -585,7 +585,7 @@ __global__ __launch_bounds__(NW * 64, 2) void split_slice_kernel(SplitArgs a) {
   bf16x8_t qr[NR > 0 ? NR : 1];
   if constexpr (FUSED) {
     __syncthreads();  // the list is complete (and the absorption's LDS is free)
-    const int np = a.s_max;  // producers (at most 16): every split of the sequence, empty or not
+    const int np = min(a.s_max, 16);  // producers: the first splits of the sequence, empty or not
     int* okp = reinterpret_cast<int*>(mbuf);
     if (w == 0) {
       const unsigned long long* fl = a.qflags + (static_cast<int64_t>(b) * a.groups + hg) * a.s_max;

@@ -12,7 +12,8 @@ from parity import say
     ("h16", 128, [1024, 700, 3, 0]),             # the split kernel absorbs the query (16 splits, most of them empty)
     ("h16", 128, [512] * 3),                     # ... 8 splits: the small merge
     ("h16", 64, [1024, 1000]),                   # ... the merge of other value dims
-    ("h16", 128, [300, 2000, 64]),               # a separate absorption
+    ("h16", 128, [300, 2000, 64]),               # ... 32 splits: the first 16 absorb it
+    ("h16", 128, [300, 5000, 64]),               # a separate absorption
     ("h16", 128, list(range(100, 1999, 50))),    # balanced schedule
     ("kv64", 64, [900, 5]),                      # fp32 matrix-core kernel
     ("kv64", 64, [300, 5]),                      # ... in one launch
@@ -52,7 +53,8 @@ def test_replays_follow_the_inputs(gpu, layer, v_dim, lens):
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("v_dim,lens", [(128, [1024, 700, 3, 0]), (128, [512] * 3), (128, [2048] * 33), (64, [1024, 1000])])
+@pytest.mark.parametrize("v_dim,lens", [(128, [1024, 700, 3, 0]), (128, [512] * 3), (128, [2048] * 33), (64, [1024, 1000]),
+                                        (128, [70, 2000])])
 def test_no_stamp_outlives_the_call(gpu, v_dim, lens):
     """A replay's stamp is the captured one: had the call left its stamps (the last words of the workspace), a replay's
     work-groups would take the previous replay's absorbed query for its own."""
@@ -64,7 +66,7 @@ def test_no_stamp_outlives_the_call(gpu, v_dim, lens):
     say(f"decode stamps d_v {v_dim} lens {lens[:4]}")
     B.run_decode(dd, workspace=ws)
     torch.cuda.synchronize()
-    splits = 8 if max(lens) in (512, 2048) else 16  # per sequence: each a producer of absorbed heads
+    splits = {512: 8, 2048: 8, 2000: 32}.get(max(lens), 16)  # per sequence, each with a stamp
     n = len(lens) * splits
     at = ws.numel() - (n * 8 + 255) // 256 * 256
     assert not ws[at:at + n * 8].any()

@@ -30,7 +30,9 @@ def test_long_batches(tok_pieces, batch, length):
 
 @pytest.mark.parametrize("batch,cap,v_dim,split", [
     (1, 64, 128, 64), (16, 1024, 128, 64), (1, 32768, 128, 256),   # one unit per wave, at most 128 partials
-    (12, 2048, 128, 128), (14, 2048, 128, 128),                    # 16 splits a sequence where 64 to 96 tokens are too many items
+    (2, 1856, 128, 64), (4, 4096, 128, 128), (3, 2080, 128, 96),   # up to 4 sequences of 4096: 32 splits at most
+    (4, 4128, 128, 96), (5, 4096, 128, 96), (1, 8192, 128, 64),    # beyond: as many as fill the chip
+    (12, 2048, 128, 128), (14, 2048, 128, 128),                    # 16 splits where 64 to 96 tokens are too many items
     (20, 600, 128, 96), (24, 1500, 128, 192), (32, 1100, 128, 160),  # 8 splits
     (20, 1600, 128, 256), (28, 2048, 128, 256), (48, 1000, 128, 256),
     (1, 1024, 64, 64), (4, 2048, 64, 128), (1, 4096, 64, 256), (1, 32768, 64, 256),  # the general merge: few partials
